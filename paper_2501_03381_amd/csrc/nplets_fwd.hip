@@ -688,7 +688,7 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
         refine_launch(sel->mode, a, ro, red, s);
     }
     if (reduce && red.topk > 0)
-        hipLaunchKernelGGL(k_red_final, dim3((unsigned)(kmax + 1), (unsigned)D), dim3(256), 0, s, red, a.hdr);
+        red_final_launch(red, a.hdr, kmax, D, s);
     return hip_status(hipGetLastError());
 }
 

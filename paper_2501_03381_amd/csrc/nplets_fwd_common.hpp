@@ -296,86 +296,6 @@ __host__ __device__ inline size_t wave_stage_bytes(int N, int kmax, bool with_bi
 }
 
 
-// ------------------------------------------------------------------------------------------------
-// Final merge of the streaming reduction: one workgroup per (order k, dataset d).
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_red_final(RedArgs red, WsHeader* hdr)
-{
-    __shared__ RedFinal S;
-    const int k = blockIdx.x, d = blockIdx.y;
-    const int K = red.topk;
-    if (K <= 0) return;
-    double* tv = red.top_val + ((int64_t)d * (red.kmax + 1) + k) * 2 * K;
-    int64_t* tg = red.top_g + ((int64_t)d * (red.kmax + 1) + k) * 2 * K;
-    for (int i = threadIdx.x; i < 2 * K; i += blockDim.x) {
-        const int l = i / K, j = i % K;
-        const bool has = tg[i] >= 0;
-        S.key[l][0][j] = has ? red_list_key(l, tv[i]) : kKeyEmpty;
-        S.g[l][0][j] = has ? tg[i] : kGEmpty;
-    }
-    if (threadIdx.x == 0) { S.cur[0] = S.cur[1] = 0; }
-    __syncthreads();
-    // Segments in batches of one per thread: each thread tests its segment's two list heads
-    // against the current K-th entries, the candidates are compacted, and only those are merged
-    // (tested again against the threshold as it tightens).  After the first batches almost no
-    // segment beats the running lists, so a batch costs one round of parallel loads.
-    __shared__ uint32_t cand[2][256];
-    __shared__ int ncand[2];
-    const uint32_t nseg = min(hdr->seg_next, red.seg_cap);
-    for (uint32_t s0 = 0; s0 < nseg; s0 += blockDim.x) {
-        if (threadIdx.x < 2) ncand[threadIdx.x] = 0;
-        __syncthreads();
-        const uint32_t s = s0 + threadIdx.x;
-        if (s < nseg) {
-            const SegHdr h = red.seg_hdr[s];
-            if (h.d == d && h.k == k) {
-                for (int l = 0; l < 2; ++l) {
-                    const int64_t e = ((int64_t)s * 2 + l) * K;
-                    const int c = S.cur[l];
-                    if (red_less(red.seg_key[e], red.seg_g[e], S.key[l][c][K - 1], S.g[l][c][K - 1]))
-                        cand[l][atomicAdd(&ncand[l], 1)] = s;
-                }
-            }
-        }
-        __syncthreads();
-        for (int l = 0; l < 2; ++l) {
-            const int nc = ncand[l];
-            for (int j = 0; j < nc; ++j) {
-                const int64_t e = ((int64_t)cand[l][j] * 2 + l) * K;
-                const uint64_t* bk = red.seg_key + e;
-                const int64_t* bg = red.seg_g + e;
-                const int c = S.cur[l];
-                if (!red_less(bk[0], bg[0], S.key[l][c][K - 1], S.g[l][c][K - 1])) continue;   // uniform
-                red_final_merge(S, l, K, bk, bg, K);
-            }
-        }
-        __syncthreads();                         // every thread has read ncand before the reset
-    }
-    const uint32_t nlate = min(hdr->late_next, red.late_cap);
-    for (uint32_t b0 = 0; b0 < nlate; b0 += blockDim.x) {
-        const uint32_t i = b0 + threadIdx.x;
-        bool mine = false;
-        double v = 0.0;
-        int64_t g = 0;
-        if (i < nlate) {
-            const LateEntry e = red.late[i];
-            mine = e.d == d && e.k == k;
-            v = e.v;
-            g = e.g;
-        }
-        red_final_offer(S, 0, K, mine, red_list_key(0, v), g);
-        red_final_offer(S, 1, K, mine, red_list_key(1, v), g);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 2 * K; i += blockDim.x) {
-        const int l = i / K, j = i % K;
-        const uint64_t key = S.key[l][S.cur[l]][j];
-        const bool has = key != kKeyEmpty;
-        tv[i] = has ? red_list_val(l, key) : __builtin_nan("");
-        tg[i] = has ? S.g[l][S.cur[l]][j] : -1;
-    }
-}
-
 __global__ void k_red_init(double* top_val, int64_t* top_g, int64_t ntop, unsigned long long* hist, int64_t nhist)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;

@@ -592,7 +592,7 @@ thoi_status launch_multi(const double* Sigma, const int32_t* N_d, const int32_t*
     if (opts->precision == THOI_FP32_REFINE)
         hipLaunchKernelGGL(k_refine_multi, dim3(512), dim3(64), refine_multi_lds(nmax, kmax), s, a, m, nmax, red);
     if (reduce && red.topk > 0)
-        hipLaunchKernelGGL(k_red_final, dim3((unsigned)(kmax + 1), (unsigned)D), dim3(256), 0, s, red, a.hdr);
+        red_final_launch(red, a.hdr, kmax, D, s);
     return hip_status(hipGetLastError());
 }
 

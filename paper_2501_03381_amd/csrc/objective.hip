@@ -109,7 +109,7 @@ thoi_status launch_objective(const void* vals, int32_t val_dtype, int64_t D, int
         hipLaunchKernelGGL(kern, dim3((unsigned)w.blocks), dim3(kObjTile), 0, s, vals, D, B, (int)kind, w.per_blk, obj,
                            ra, hdr);
     }
-    if (red && red->topk > 0) hipLaunchKernelGGL(k_red_final, dim3(1, 1), dim3(256), 0, s, ra, hdr);
+    if (red && red->topk > 0) red_final_launch(ra, hdr, 0, 1, s);
     return hip_status(hipGetLastError());
 }
 

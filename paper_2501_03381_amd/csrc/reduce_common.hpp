@@ -304,77 +304,9 @@ __device__ __forceinline__ void red_end(RedLds& S, const RedArgs& r, WsHeader* h
     __syncthreads();
 }
 
-// ------------------------------------------------------------------------------------------------
-// Final merge (one workgroup per (order, dataset)): two double-buffered lists in LDS.
-// ------------------------------------------------------------------------------------------------
-struct RedFinal {
-    uint64_t key[2][2][kRedMaxK];
-    int64_t g[2][2][kRedMaxK];
-    uint64_t ck[256];
-    int64_t cg[256];
-    int cur[2];
-    int nc;
-};
-
-// Whole workgroup: merge the sorted run (bk, bg)[0..nb) into list `l`, keeping K.
-__device__ __forceinline__ void red_final_merge(RedFinal& S, int l, int K, const uint64_t* bk, const int64_t* bg, int nb)
-{
-    const int c = S.cur[l];
-    const uint64_t* ak = S.key[l][c];
-    const int64_t* ag = S.g[l][c];
-    uint64_t* ok = S.key[l][c ^ 1];
-    int64_t* og = S.g[l][c ^ 1];
-    const int na = K;
-    for (int i = threadIdx.x; i < K; i += blockDim.x) {
-        int lo = i - nb > 0 ? i - nb : 0, hi = i < na ? i : na;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (red_less(ak[mid], ag[mid], bk[i - 1 - mid], bg[i - 1 - mid])) lo = mid + 1; else hi = mid;
-        }
-        const int a = lo, b = i - a;
-        const bool takeA = (b >= nb) || (a < na && red_less(ak[a], ag[a], bk[b], bg[b]));
-        ok[i] = takeA ? ak[a] : bk[b];
-        og[i] = takeA ? ag[a] : bg[b];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) S.cur[l] = c ^ 1;
-    __syncthreads();
-}
-
-// Whole workgroup (blockDim <= 256): offer one (key, g) per thread (valid == false: nothing) to
-// list l; the candidates are compacted, sorted (bitonic) and merged.
-__device__ __forceinline__ void red_final_offer(RedFinal& S, int l, int K, bool valid, uint64_t key, int64_t g)
-{
-    const int c = S.cur[l];
-    const bool cand = valid && red_less(key, g, S.key[l][c][K - 1], S.g[l][c][K - 1]);
-    if (!__syncthreads_or(cand)) return;
-    if (threadIdx.x == 0) S.nc = 0;
-    __syncthreads();
-    if (cand) {
-        const int slot = atomicAdd(&S.nc, 1);
-        S.ck[slot] = key;
-        S.cg[slot] = g;
-    }
-    __syncthreads();
-    const int nc = S.nc;
-    int P = 1;
-    while (P < nc) P <<= 1;
-    for (int i = nc + threadIdx.x; i < P; i += blockDim.x) { S.ck[i] = kKeyEmpty; S.cg[i] = kGEmpty; }
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < (P >> 1); i += blockDim.x) {
-                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-                const bool asc = (lo & size) == 0;
-                const uint64_t ka = S.ck[lo], kb = S.ck[hi];
-                const int64_t ga = S.cg[lo], gb = S.cg[hi];
-                if (red_less(kb, gb, ka, ga) == asc) { S.ck[lo] = kb; S.ck[hi] = ka; S.cg[lo] = gb; S.cg[hi] = ga; }
-            }
-        }
-    }
-    __syncthreads();
-    red_final_merge(S, l, K, S.ck, S.cg, nc < K ? nc : K);
-}
+// Final merge of a reduction's segments and queued values into top_val / top_g (reduce_final.hip):
+// orders 0..kmax of D datasets.
+void red_final_launch(const RedArgs& red, WsHeader* hdr, int kmax, int64_t D, hipStream_t s);
 
 // One thread: queue an FP64-refined value for the final merge and count it in the histogram.
 __device__ __forceinline__ void red_late(const RedArgs& r, WsHeader* hdr, int d, int k, int64_t g, double v)

@@ -1,0 +1,40 @@
+"""The final merge of the streaming reduction at the edges of its selection: fewer segments than
+wavefronts, fewer than K, more than one batch of segments, full and partial lists, and values with
+many ties (ordered by the lower index).  The lists are an exact selection, so no tolerance."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def lists(v, K):
+    """(values, indices) of the K largest and K smallest, ties by the lower index."""
+    i = np.arange(len(v))
+    top, bot = np.lexsort((i, -v))[:K], np.lexsort((i, v))[:K]
+    return (v[top], top), (v[bot], bot)
+
+
+# 256 values per segment up to 4096 segments, more beyond
+@pytest.mark.parametrize("B", [1, 40, 3 * 256, 9 * 256 + 1, 130 * 256 + 7, 2050 * 256, 4096 * 256 + 300])
+@pytest.mark.parametrize("K", [1, 7, 100, 256])
+@pytest.mark.parametrize("ties", [False, True])
+def test_final_merge_is_an_exact_selection(B, K, ties):
+    import torch
+    from paper_2501_03381_amd import api
+    print(f"[gpu-case] final merge B={B} K={K} ties={ties}", flush=True)
+    rng = np.random.default_rng(B + K)
+    v = np.round(rng.standard_normal(B), 1) if ties else np.sort(rng.standard_normal(B))
+    if B > 100:
+        v[rng.integers(0, B, 5)] = np.nan                   # not counted
+    st = None
+    for part in np.array_split(np.arange(B), 2):            # the second call merges into the first's lists
+        x = np.full(B, np.nan)
+        x[part] = v[part]
+        _, st = api.objective(torch.from_numpy(x[None]).cuda(), "mean", write=False, topk=K, state=st)
+    tv, tg, _ = st.result()
+    ref = np.where(np.isnan(v), np.nan, v)
+    keep = np.nonzero(~np.isnan(ref))[0]
+    for l, (val, idx) in enumerate(lists(ref[keep], K)):
+        n = len(val)
+        assert np.array_equal(tg[0, 0, l, :n], keep[idx]) and np.array_equal(tv[0, 0, l, :n], val)
+        assert np.all(tg[0, 0, l, n:] == -1)
