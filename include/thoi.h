@@ -313,8 +313,8 @@ size_t thoi_objective_workspace_bytes(int64_t D, int64_t B, const thoi_reduce* r
  *   cur_mask, best_mask: device [kappa][2] uint64; cur_omega, best_omega: device [kappa] FP64;
  *     accepted: device [kappa] int64 (the final state, the best state and the number of accepted
  *     moves per chain).
- * 1 <= k_min <= k_max <= min(N - 1, 64); T0 > 0, alpha > 0.  Every iteration is one kernel launch on
- * `stream`; nothing is allocated and the host does not wait.
+ * 1 <= k_min <= k_max <= min(N - 1, 64); T0 > 0, alpha > 0.  Every 256 iterations are one kernel
+ * launch on `stream`; nothing is allocated and the host does not wait.
  */
 thoi_status thoi_anneal(const double* Sigma, int32_t N, const uint64_t* masks0, int32_t kappa, int32_t iters,
                         const double* draw_move, const double* draw_a, const double* draw_b, const double* draw_accept,

@@ -15,19 +15,15 @@
 #include "thoi_internal.hpp"
 #include "nplets_common.hpp"
 #include "objective_common.hpp"
-#include "pair_factor.hpp"
+#include "pair_factor_lat.hpp"
+#include "search_mask.hpp"
 
 namespace thoi {
 namespace {
 
 constexpr int kSelThreads = 1024;
+constexpr int kLatWaves = 2048;         // wavefronts of an order up to which the evaluation is latency-bound
 constexpr int kSelMax = 4096;           // candidates of one order that the selection sorts in LDS
-
-struct Mask {
-    uint64_t w[2];
-};
-
-__device__ __forceinline__ int popc(const Mask& m) { return __popcll(m.w[0]) + __popcll(m.w[1]); }
 
 __device__ __forceinline__ bool has(const Mask& m, int v) { return (m.w[v >> 6] >> (v & 63)) & 1ull; }
 
@@ -107,20 +103,7 @@ __global__ __launch_bounds__(64) void k_greedy_eval(GreedyArgs g, int s, int kc)
     k = k < 64 ? k : 64;
     int ci = 0;
     if (lane < k) {
-        // lane j takes the (j+1)-th member
-        Mask m = C;
-        int n = lane;
-        ci = 0;
-        for (int h = 0; h < 2; ++h) {
-            const int c = __popcll(m.w[h]);
-            if (n < c) {
-                uint64_t x = m.w[h];
-                for (int i = 0; i < n; ++i) x &= x - 1;
-                ci = 64 * h + __builtin_ctzll(x);
-                break;
-            }
-            n -= c;
-        }
+        ci = nth_set(C, lane);                 // lane j takes the (j+1)-th member
         cidx[lane] = ci;
         const double dj = Sig[(int64_t)ci * N + ci];
         sIsd[lane] = dj > 0.0 ? 1.0 / sqrt(dj) : __builtin_nan("");
@@ -140,7 +123,11 @@ __global__ __launch_bounds__(64) void k_greedy_eval(GreedyArgs g, int s, int kc)
 
 // grid (ceil(kappa * N / 2), D), block 64: two candidate slots per wavefront (half-wave h takes
 // slot 2 blockIdx.x + h), factored with the rows in registers; for steps whose order is at most
-// kW2Max.  The same candidates, measures and sums in variable order as k_greedy_eval.
+// kW2Max.  The same candidates, measures and sums in variable order as k_greedy_eval.  LAT: the
+// factorisation arranged for latency, for up to about one wavefront per SIMD (N = 100, 16 solutions,
+// one dataset, orders 4..32: 2.03 ms against 2.13); with more of them its registers cost more than it
+// gains (200 datasets of 40 variables, 32 solutions, orders 4..30: 22.3 ms against 20.2).
+template <bool LAT>
 __global__ __launch_bounds__(64) void k_greedy_eval_pair(GreedyArgs g, int s)
 {
     __shared__ double scol[2 * 2 * kW2Max], swrow[2 * 2 * kW2Max];
@@ -171,25 +158,15 @@ __global__ __launch_bounds__(64) void k_greedy_eval_pair(GreedyArgs g, int s)
     int kh = use ? popc(C) : 0;
     kh = kh < kW2Max ? kh : kW2Max;
     int* ch = sch + h * kW2Max;
-    if (i < kh) {
-        Mask m = C;
-        int n = i, ci = 0;
-        for (int hw = 0; hw < 2; ++hw) {
-            const int c = __popcll(m.w[hw]);
-            if (n < c) {
-                uint64_t x = m.w[hw];
-                for (int t = 0; t < n; ++t) x &= x - 1;
-                ci = 64 * hw + __builtin_ctzll(x);
-                break;
-            }
-            n -= c;
-        }
-        ch[i] = ci;
-    }
+    if (i < kh) ch[i] = nth_set(C, i);
     wave_sync();
     const int k0 = __shfl(kh, 0), k1 = __shfl(kh, 32);
-    const FactorOut<double> f = pair_factor<true, true>(Sig, N, ch, k0 > k1 ? k0 : k1, kh, scol + h * 2 * kW2Max,
-                                                        swrow + h * 2 * kW2Max);
+    const int ku = k0 > k1 ? k0 : k1;
+    double* col = scol + h * 2 * kW2Max;
+    double* wrow = swrow + h * 2 * kW2Max;
+    FactorOut<double> f;
+    if constexpr (LAT) f = pair_factor_lat<PairSource::Global, true>(Sig, N, ch, ku, kh, col, wrow);
+    else f = pair_factor<true, true>(Sig, N, ch, ku, kh, col, wrow);
     if (i == 0 && slot < nslot) {
         if (!use) {
             meas[slot] = __builtin_nan("");
@@ -325,11 +302,12 @@ thoi_status launch_greedy(const double* Sigma, int64_t D, int32_t N, int32_t k_f
     char* base = static_cast<char*>(ws);
     g.cmask = reinterpret_cast<Mask*>(base);
     g.meas = reinterpret_cast<double*>(base + (size_t)kappa * N * sizeof(Mask));
+    const int64_t waves = ((int64_t)kappa * N + 1) / 2 * D;
+    const auto eval_pair = waves <= kLatWaves ? k_greedy_eval_pair<true> : k_greedy_eval_pair<false>;
     for (int32_t t = 0; t < steps; ++t) {
         // step t builds order k_first + t + 1
         if (k_first + t + 1 <= kW2Max)
-            hipLaunchKernelGGL(k_greedy_eval_pair, dim3((unsigned)((kappa * N + 1) / 2), (unsigned)D), dim3(64), 0, s, g,
-                               (int)t);
+            hipLaunchKernelGGL(eval_pair, dim3((unsigned)((kappa * N + 1) / 2), (unsigned)D), dim3(64), 0, s, g, (int)t);
         else {
             const int kc = k_first + t + 1;
             const size_t lds = (size_t)kc * (size_t)(kc + 1) * sizeof(double);

@@ -289,7 +289,7 @@ def anneal(Sigma: torch.Tensor, masks0: np.ndarray, draws: dict, T0: float = 1.0
     count per chain).
 
     on_device (default: with precision "fp64", N <= 128 and orders <= 64): the whole run goes to
-    the device in one call (thoi_anneal: one kernel launch per iteration, no host round trip);
+    the device in one call (thoi_anneal: 256 iterations per kernel launch, no host round trip);
     otherwise every iteration evaluates its proposals with one batched evaluator call and decides
     on the host.
     """
