@@ -352,6 +352,14 @@ thoi_status thoi_reduce_init(const thoi_reduce* red, int64_t D, int32_t kmax, vo
 /* Device workspace bytes needed by the call `which` (THOI_WS_*); 0 if none. */
 size_t thoi_workspace_bytes(int32_t which, int64_t D, int64_t T, int32_t N,
                             const thoi_nplets* sel, const thoi_eval_opts* opts);
+/*
+ * Workspace with which thoi_nplets_eval may also take engines that keep a table (never less than
+ * thoi_workspace_bytes(THOI_WS_EVAL, ...), which stays enough for every call): with THOI_ENGINE_AUTO,
+ * an FP64 streaming reduction over whole orders of 21..30 variables then runs on a table of log det
+ * over all subsets, 2^(N+3) bytes (8 GB at N = 30; several datasets at a time up to 256 MB), instead
+ * of one factorisation per n-plet.  Same results to rounding.
+ */
+size_t thoi_eval_workspace_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
 /* Offset in bytes of the int32 device status word inside a workspace. */
 size_t thoi_ws_status_offset(void);
 

@@ -39,6 +39,19 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
+def _eval_workspace(D: int, N: int, sel: B.ThoiNplets, opts: B.ThoiEvalOpts, device) -> torch.Tensor:
+    """The workspace of an evaluation call: with the tables of the engines that keep one when the device
+    has the memory for them, else the least that the call needs."""
+    least = B.thoi_workspace_bytes(B.THOI_WS_EVAL, D, 0, N, sel, opts)
+    full = B.thoi_eval_workspace_bytes_full(D, N, sel, opts)
+    if full > least:
+        try:
+            return _workspace(full, device)
+        except torch.OutOfMemoryError:
+            pass
+    return _workspace(least, device)
+
+
 def device_status(ws: torch.Tensor) -> int:
     """The int32 status word a call left in its workspace (synchronises)."""
     off = B.thoi_ws_status_offset()
@@ -346,8 +359,7 @@ def nplets_reduce(Sigma: torch.Tensor, *, orders=None, g_range=None, nplets=None
         raise ValueError("state does not match this selection")
     opts = make_opts(precision, torch.float32, vif_tau, bias_correct, T, False, engine=engine)
     opts.reduce = ctypes.pointer(state.struct)
-    nb = B.thoi_workspace_bytes(B.THOI_WS_EVAL, D, 0, N, sel, opts)
-    ws = _workspace(nb, S.device)
+    ws = _eval_workspace(D, N, sel, opts, S.device)
     B.thoi_nplets_eval(_ptr(S), D, N, sel, opts, None, _ptr(flags), _ptr(ws), ws.numel(), _stream(S.device))
     if check:
         raise_on_device_status(ws, "thoi_nplets_eval")

@@ -33,7 +33,8 @@ THOI_NOALLOC_SCRATCH_BYTES = 32 << 20
 
 EXPORTS = [
     "thoi_copulize", "thoi_cov", "thoi_nplets_eval", "thoi_nplets_eval_backward", "thoi_reduce_init",
-    "thoi_workspace_bytes", "thoi_ws_status_offset", "thoi_count", "thoi_unrank_host", "thoi_bias_offsets",
+    "thoi_workspace_bytes", "thoi_eval_workspace_bytes_full", "thoi_ws_status_offset", "thoi_count",
+    "thoi_unrank_host", "thoi_bias_offsets",
     "thoi_status_string", "thoi_version", "thoi_nplets_eval_multi", "thoi_multi_offsets",
     "thoi_multi_workspace_bytes", "thoi_objective", "thoi_objective_workspace_bytes", "thoi_eval_launch_shape",
     "thoi_nplets_eval_noalloc", "thoi_anneal", "thoi_greedy", "thoi_greedy_workspace_bytes",
@@ -109,6 +110,8 @@ def lib():
     L.thoi_reduce_init.argtypes = [ctypes.POINTER(ThoiReduce), I64, I32, P]
     L.thoi_workspace_bytes.argtypes = [I32, I64, I64, I32, NP, OP]
     L.thoi_workspace_bytes.restype = SZ
+    L.thoi_eval_workspace_bytes_full.argtypes = [I64, I32, NP, OP]
+    L.thoi_eval_workspace_bytes_full.restype = SZ
     L.thoi_ws_status_offset.argtypes = []
     L.thoi_ws_status_offset.restype = SZ
     L.thoi_count.argtypes = [I32, I32, I32]
@@ -233,6 +236,10 @@ def thoi_eval_launch_shape(N, sel: ThoiNplets, opts: ThoiEvalOpts):
 def thoi_workspace_bytes(which, D, T, N, sel=None, opts=None) -> int:
     return int(lib().thoi_workspace_bytes(which, D, T, N, ctypes.byref(sel) if sel is not None else None,
                                           ctypes.byref(opts) if opts is not None else None))
+
+
+def thoi_eval_workspace_bytes_full(D, N, sel, opts) -> int:
+    return int(lib().thoi_eval_workspace_bytes_full(D, N, ctypes.byref(sel), ctypes.byref(opts)))
 
 
 def thoi_ws_status_offset() -> int:

@@ -414,6 +414,11 @@ size_t thoi_workspace_bytes(int32_t which, int64_t D, int64_t T, int32_t N, cons
     }
 }
 
+size_t thoi_eval_workspace_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts)
+{
+    return (sel && opts && D >= 0) ? eval_ws_bytes_full(D, N, sel, opts) : 0;
+}
+
 size_t thoi_ws_status_offset(void) { return 0; }
 
 int64_t thoi_count(int32_t N, int32_t kmin, int32_t kmax) { return count_orders(N, kmin, kmax); }

@@ -65,7 +65,7 @@ extern "C" thoi_status thoi_nplets_eval_noalloc(const double* Sigma, int64_t D, 
     void* ws = nullptr;
     const thoi_status sst = scratch_for(s, &ws);
     if (sst != THOI_OK) return sst;
-    const thoi_status lst = launch_eval(Sigma, D, N, sel, opts, out, flags, ws, kScratchBytes, s, true);
+    const thoi_status lst = launch_eval(Sigma, D, N, sel, opts, out, flags, ws, need, s, true);
     if (lst != THOI_OK || status == nullptr) return lst;
     hipLaunchKernelGGL(k_copy_status, dim3(1), dim3(64), 0, s, static_cast<const WsHeader*>(ws), status);
     return hip_status(hipGetLastError());

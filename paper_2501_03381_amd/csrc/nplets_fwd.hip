@@ -14,6 +14,7 @@
 // a follow-up FP64 kernel re-evaluates exactly those and overwrites their results.
 // Results go either to the output planes or to the streaming reducer (reduce_common.hpp).
 #include "nplets_fwd_common.hpp"
+#include "nplets_cube.hpp"
 #include "nplets_prefix.hpp"
 #include "nplets_wave2.hpp"
 
@@ -390,11 +391,12 @@ Plan make_plan(int N, int64_t D, const thoi_nplets* sel, bool reduce, const thoi
 
 struct EvalWs {
     size_t refine_off, korder_off, cnt_off, base_off, blk0_off, cursor_off, perm_off;
-    size_t seg_key_off, seg_g_off, seg_hdr_off, late_off, bound_off, clear_end, total;
+    size_t seg_key_off, seg_g_off, seg_hdr_off, late_off, bound_off, clear_end, table_off, total;
     uint32_t refine_cap, seg_cap, late_cap;
 };
 
-EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts)
+// cube: the layout with the subset table of the cube engine (for calls that want it).
+EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts, bool cube)
 {
     EvalWs w{};
     const int64_t B = sel_B(sel);
@@ -425,7 +427,8 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         const int K = opts->reduce->topk;
         const Plan P = opts->precision == THOI_FP64 ? make_plan<double>(N, D, sel, true, opts)
                                                     : make_plan<float>(N, D, sel, true, opts);
-        const int64_t segs = P.seg_cap * D;
+        int64_t segs = P.seg_cap * D;
+        if (cube) segs = cube_segments(N, sel->kmin, sel->kmax) * D;
         w.seg_cap = (uint32_t)(segs > 0 ? segs : 1);
         w.seg_key_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);
         w.seg_g_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);
@@ -433,6 +436,7 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         w.late_cap = w.refine_cap;
         if (w.late_cap) { w.late_off = off; off = align_up(off + (size_t)w.late_cap * sizeof(LateEntry), 256); }
     }
+    if (cube) { w.table_off = off; off = align_up(off + cube_table_bytes(N, D), 256); }
     w.total = off;
     return w;
 }
@@ -575,7 +579,15 @@ void launch_forward(EvalArgs& a, const thoi_nplets* sel, const Plan& P, const Re
 
 size_t eval_ws_bytes(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts)
 {
-    return eval_layout(D, N, sel, opts).total;
+    return eval_layout(D, N, sel, opts, false).total;
+}
+
+size_t eval_ws_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts)
+{
+    const size_t least = eval_ws_bytes(D, N, sel, opts);
+    if (!cube_wanted(N, D, sel, opts)) return least;
+    const size_t full = eval_layout(D, N, sel, opts, true).total;
+    return full > least ? full : least;
 }
 
 // Largest LDS footprint any kernel of this call needs (the host rejects calls above the limit).
@@ -601,8 +613,10 @@ size_t eval_lds_bytes(int32_t N, const thoi_nplets* sel, const thoi_eval_opts* o
 thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts,
                         void* out, uint8_t* flags, void* ws, size_t ws_bytes, hipStream_t s, bool serial)
 {
-    const EvalWs w = eval_layout(D, N, sel, opts);
+    EvalWs w = eval_layout(D, N, sel, opts, false);
     if (ws == nullptr || ws_bytes < w.total) return THOI_EWORKSPACE;
+    const bool cube = cube_wanted(N, D, sel, opts) && ws_bytes >= eval_ws_bytes_full(D, N, sel, opts);
+    if (cube) w = eval_layout(D, N, sel, opts, true);
     char* base = static_cast<char*>(ws);
     const bool reduce = opts->reduce != nullptr;
     EvalArgs a{};
@@ -656,7 +670,9 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
     ws_clear(base, w.clear_end, s);
     if (D == 0 || a.B == 0) return hip_status(hipGetLastError());
 
-    if (opts->precision == THOI_FP64) {
+    if (cube) {
+        cube_launch(a, red, sel->kmin, sel->kmax, reinterpret_cast<double*>(base + w.table_off), s);
+    } else if (opts->precision == THOI_FP64) {
         Plan P = make_plan<double>(N, D, sel, reduce, opts);
         P.serial = serial;
         a.seg_tiles = P.seg_tiles;

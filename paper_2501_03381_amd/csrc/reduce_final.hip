@@ -8,6 +8,7 @@
 // the other (two dependent global reads and two barriers each) took 285 us for the 236 segments
 // of an objective over 60,458 n-plets with K = 100; the whole call of 64 datasets and that objective
 // went from 482 to 215 us, the FP64 reduction of 25 variables from 4.70 to 4.31 ms.
+#include "radix_pick.hpp"
 #include "reduce_common.hpp"
 
 namespace thoi {
@@ -91,28 +92,10 @@ __device__ __forceinline__ uint64_t red_final_select(RedFinal& S, int n, int K)
         const uint32_t pre = S.prefix;
         for (int i = threadIdx.x; i < n; i += kFinThreads) {
             const uint32_t h = (uint32_t)(S.head[i] >> 32);
-            if (pass == 3 || (h >> (8 * (pass + 1))) == (pre >> (8 * (pass + 1)))) atomicAdd(&S.rh[(h >> (8 * pass)) & 255u], 1u);
+            if (radix_match(h, pre, pass)) atomicAdd(&S.rh[(h >> (8 * pass)) & 255u], 1u);
         }
         __syncthreads();
-        if (threadIdx.x < 64) {
-            // lane t sums bins 4t .. 4t+3; the lane whose running sum first reaches the rank picks
-            const int t = (int)threadIdx.x;
-            uint32_t v[4], own = 0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { v[u] = S.rh[4 * t + u]; own += v[u]; }
-            uint32_t incl = own;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) { const uint32_t y = __shfl_up(incl, o, 64); incl += t >= o ? y : 0; }
-            const uint32_t r = (uint32_t)S.rank;
-            const uint64_t m = __ballot(incl >= r);
-            if (t == __builtin_ctzll(m)) {
-                uint32_t before = incl - own;
-                int u = 0;
-                while (u < 3 && before + v[u] < r) before += v[u++];
-                S.prefix = pre | ((uint32_t)(4 * t + u) << (8 * pass));
-                S.rank = (int)(r - before);
-            }
-        }
+        if (threadIdx.x < 64) radix_pick(S.rh, (int)threadIdx.x, pass, S.prefix, S.rank);
         __syncthreads();
     }
     return ((uint64_t)S.prefix << 32) | 0xffffffffull;

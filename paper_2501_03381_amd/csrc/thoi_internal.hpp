@@ -75,6 +75,7 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
 thoi_status check_eval(const double* Sigma, int64_t D, int32_t N, const thoi_nplets* sel,
                        const thoi_eval_opts* opts, bool forward, const void* out);
 size_t eval_ws_bytes(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
+size_t eval_ws_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
 size_t eval_lds_bytes(int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
 void eval_launch_shape(int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts, int32_t* n_launches,
                        int64_t* max_items_x);

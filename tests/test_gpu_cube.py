@@ -1,0 +1,108 @@
+"""Subset-table engine of whole-order FP64 reductions (21..30 variables) against one factorisation per n-plet
+(engine="factor"): the same lists and histograms, values to 1e-9 (the FP64 tolerance of the evaluation tests).
+No value of these inputs lies within rounding of a bin edge or of another list entry, so indices and counts
+are compared exactly."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2501_03381_amd import api, binding, synth
+    return torch, api, binding, synth
+
+
+def sigma(torch, synth, N, D, seed=0):
+    rng = np.random.default_rng(1000 * N + seed)
+    return torch.from_numpy(np.stack([np.cov(synth.factor_model(rng, 3000, N, 5).T) for _ in range(D)])).cuda()
+
+
+def both(api, S, kmin, kmax, **kw):
+    r = [api.nplets_reduce(S, orders=(kmin, kmax), precision="fp64", engine=e, **kw).result() for e in ("factor", "auto")]
+    return r
+
+
+def same(a, b):
+    assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+    assert np.array_equal(np.isnan(a[0]), np.isnan(b[0]))
+    assert np.abs(np.nan_to_num(a[0]) - np.nan_to_num(b[0])).max() <= 1e-9
+
+
+# orders that start or end inside a row, a single order, every order, several datasets
+@pytest.mark.parametrize("N,kmin,kmax,D,K,bins", [
+    (21, 3, 21, 1, 100, 256), (21, 3, 8, 2, 1, 16), (21, 10, 10, 1, 256, 8), (22, 3, 22, 3, 64, 64),
+    (22, 12, 22, 1, 65, 0), (23, 3, 11, 1, 0, 4096), (24, 3, 24, 1, 7, 32)])
+def test_cube_matches_factorisation(env, N, kmin, kmax, D, K, bins):
+    torch, api, B, synth = env
+    print(f"[gpu-case] cube N={N} orders {kmin}..{kmax} D={D} K={K} bins={bins}", flush=True)
+    S = sigma(torch, synth, N, D)
+    kw = dict(topk=K, hist_bins=bins, hist_range=(-7.3, 5.1))
+    a, b = both(api, S, kmin, kmax, **kw)
+    if K == 0:
+        a, b = [(np.zeros(1), np.zeros(1), x[2]) for x in (a, b)]
+    if bins == 0:
+        a, b = [(x[0], x[1], np.zeros(1)) for x in (a, b)]
+    same(a, b)
+
+
+def test_cube_bias_flags_and_not_positive_definite(env):
+    torch, api, B, synth = env
+    N = 21
+    S = sigma(torch, synth, N, 1)
+    S[0, 3, 18] = S[0, 18, 3] = 2.0 * torch.sqrt(S[0, 3, 3] * S[0, 18, 18])   # every superset of {3, 18} fails
+    n = B.thoi_count(N, 3, N)
+    fl = [torch.zeros((1, n), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    r = []
+    for e, f in zip(("factor", "auto"), fl):
+        print(f"[gpu-case] cube not positive definite, bias, {e}", flush=True)
+        r.append(api.nplets_reduce(S, orders=(3, N), precision="fp64", engine=e, topk=20, hist_bins=32,
+                                   hist_range=(-7.3, 5.1), bias_correct=True, T=500, flags=f).result())
+    same(*r)
+    assert torch.equal(fl[0], fl[1]) and int((fl[1] == B.THOI_NPLET_NOT_PD).sum()) == 2 ** (N - 2) - 1
+
+
+def test_cube_accumulates_and_takes_the_least_workspace(env):
+    torch, api, B, synth = env
+    N = 21
+    S = sigma(torch, synth, N, 2, 1)
+    sel = api.range_selection(N, 3, N)
+    res = []
+    for full in (False, True):
+        print(f"[gpu-case] cube workspace full={full}", flush=True)
+        st = api.ReduceState(1, N, 30, 64, (-7.3, 5.1), S.device)
+        o = api.make_opts("fp64", torch.float32)
+        o.reduce = ctypes.pointer(st.struct)
+        least = B.thoi_workspace_bytes(B.THOI_WS_EVAL, 1, 0, N, sel, o)
+        most = B.thoi_eval_workspace_bytes_full(1, N, sel, o)
+        assert most > least + (8 << N) // 2
+        ws = torch.empty(most if full else least, dtype=torch.uint8, device="cuda")
+        for d in range(2):                       # the second call merges into the lists of the first
+            B.thoi_nplets_eval(api._ptr(S[d].contiguous()), 1, N, sel, o, None, None, api._ptr(ws), ws.numel(),
+                               api._stream(S.device))
+        torch.cuda.synchronize()
+        assert api.device_status(ws) == B.THOI_OK
+        res.append(st.result())
+    same(*res)
+
+
+def test_exchangeable_variables_tie_by_index(env):
+    """Equal sub-matrices give equal values: of a compound-symmetric matrix every n-plet of an order ties, so
+    the lists are the first indices of the order."""
+    torch, api, B, synth = env
+    N = 21
+    S = torch.full((1, N, N), 0.25, dtype=torch.float64, device="cuda") + 0.75 * torch.eye(N, dtype=torch.float64, device="cuda")
+    print("[gpu-case] cube ties", flush=True)
+    tv, tg, h = api.nplets_reduce(S, orders=(3, N), precision="fp64", topk=10, hist_bins=16, hist_range=(-7.3, 5.1)).result()
+    g = 0
+    for k in range(3, N + 1):
+        n = B.thoi_count(N, k, k)
+        m = min(n, 10)
+        for l in range(2):
+            assert np.array_equal(tg[0, k, l, :m], np.arange(g, g + m)) and len(set(tv[0, k, l, :m])) == 1
+        assert h[0, k].max() == n == h[0, k].sum()
+        g += n
