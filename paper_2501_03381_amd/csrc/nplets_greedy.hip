@@ -16,6 +16,7 @@
 #include "nplets_common.hpp"
 #include "objective_common.hpp"
 #include "pair_factor_lat.hpp"
+#include "radix_pick.hpp"
 #include "search_mask.hpp"
 
 namespace thoi {
@@ -191,9 +192,14 @@ __device__ __forceinline__ bool sel_before(uint64_t kx, int ix, uint64_t ky, int
 }
 
 // grid 1, block kSelThreads: the objective of each of the ncand = kappa * N slots of step s, then
-// order them and keep the kappa best distinct n-plets as step s + 1.
+// the kappa best distinct n-plets in order as step s + 1.
 //
-// Bitonic sort in LDS of the P >= ncand (a power of two) keys and slot indices.  Thread
+// Selection before sorting: a radix selection over the upper key words (four passes of 8 bits) finds a
+// key that kappa slots reach, and only the slots up to it (kappa and the ties of that word) are
+// sorted.  Sorting all 1600 slots of a step took 19.6 us of which the sort is most; see launch_greedy
+// for the figures.
+//
+// The sort: bitonic in LDS of the P >= n (a power of two) keys and slots.  Thread
 // 1024 j + 64 w + r of a stage with stride <= 64 exchanges entries of the 128-entry chunk
 // 2048 j + 128 w only, so between two such stages wavefront w waits for itself alone; a stage that
 // follows or precedes one with a wider stride (or the fill) waits for the block.  When kappa <= 128
@@ -205,18 +211,61 @@ __device__ __forceinline__ bool sel_before(uint64_t kx, int ix, uint64_t ky, int
 __global__ __launch_bounds__(kSelThreads) void k_greedy_select(GreedyArgs g, int s)
 {
     __shared__ uint64_t key[kSelMax];
-    __shared__ int idx[kSelMax];
-    __shared__ Mask msk[kSelMax];           // the n-plets by slot, read for the lexicographic ties
+    __shared__ int idx[kSelMax];            // entry (into msk) ...
+    __shared__ Mask msk[kSelMax];           // ... its n-plet, read for the lexicographic ties
+    __shared__ int slot_of[kSelMax];        // ... and its candidate slot
+    __shared__ uint32_t rh[256];
+    __shared__ uint32_t sprefix;
+    __shared__ int srank, sn;
+    constexpr int kPer = kSelMax / kSelThreads;
     const int ncand = g.kappa * g.N;
-    int P = 1;
-    while (P < ncand) P <<= 1;
-    for (int i = threadIdx.x; i < P; i += kSelThreads) {
+    const int tid = threadIdx.x;
+    uint64_t kk[kPer];
+    int nv = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = tid + u * kSelThreads;
         const double o = i < ncand ? objective_of<double>(g.meas, g.D, ncand, i, g.kind) : __builtin_nan("");
-        // ascending key = better first; invalid slots last
-        key[i] = isnan(o) ? ~0ull : (g.sign > 0.0 ? ~okey(o) : okey(o));
-        idx[i] = i < ncand ? i : -1;
-        msk[i] = isnan(o) ? Mask{{0ull, 0ull}} : g.cmask[i];
+        // ascending key = better first; invalid slots are left out
+        kk[u] = isnan(o) ? ~0ull : (g.sign > 0.0 ? ~okey(o) : okey(o));
     }
+    if (tid == 0) { sprefix = 0; srank = g.kappa; sn = 0; }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) nv += __syncthreads_count(kk[u] != ~0ull);
+    uint32_t upto = 0xffffffffu;
+    if (nv > g.kappa) {                     // uniform
+        for (int pass = 3; pass >= 0; --pass) {
+            if (tid < 256) rh[tid] = 0;
+            __syncthreads();
+            const uint32_t pre = sprefix;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const uint32_t h = (uint32_t)(kk[u] >> 32);
+                if (kk[u] != ~0ull && radix_match(h, pre, pass))
+                    atomicAdd(&rh[(h >> (8 * pass)) & 255u], 1u);
+            }
+            __syncthreads();
+            if (tid < 64) radix_pick(rh, tid, pass, sprefix, srank);
+            __syncthreads();
+        }
+        upto = sprefix;
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (kk[u] != ~0ull && (uint32_t)(kk[u] >> 32) <= upto) {
+            const int e = atomicAdd(&sn, 1);
+            const int i = tid + u * kSelThreads;
+            key[e] = kk[u];
+            idx[e] = e;
+            msk[e] = g.cmask[i];
+            slot_of[e] = i;
+        }
+    }
+    __syncthreads();
+    const int nsel = sn;
+    int P = 1;
+    while (P < nsel) P <<= 1;
+    for (int i = nsel + tid; i < P; i += kSelThreads) { key[i] = ~0ull; idx[i] = -1; }
     const bool topk = g.kappa <= kSelChunk && P > kSelChunk;
     const int top = topk ? kSelChunk : P;
     bool wide = true;
@@ -266,11 +315,11 @@ __global__ __launch_bounds__(kSelThreads) void k_greedy_select(GreedyArgs g, int
     // the valid slots come first and are distinct n-plets: the first min(kappa, valid) are kept,
     // one thread each
     const int t = threadIdx.x;
-    const int n = __syncthreads_count(t < g.kappa && t < P && key[t] != ~0ull);
+    const int n = nsel < g.kappa ? nsel : g.kappa;
     if (t < n) {
         const int i = idx[t];
         g.sols[(int64_t)(s + 1) * g.kappa + t] = msk[i];
-        g.vals[(int64_t)(s + 1) * g.kappa + t] = objective_of<double>(g.meas, g.D, ncand, i, g.kind);
+        g.vals[(int64_t)(s + 1) * g.kappa + t] = objective_of<double>(g.meas, g.D, ncand, slot_of[i], g.kind);
     }
     if (t == 0) g.count[s + 1] = n;
 }
