@@ -21,18 +21,30 @@ gradient comes from the HIP kernels (LIST selection, streaming top-K reduction, 
 """
 from __future__ import annotations
 
+import math
+
 import numpy as np
 import torch
 
 from . import api, binding as B
 
 
-def _rows_to_device(rows: np.ndarray, device) -> torch.Tensor:
+def _rows_to_device(rows, device) -> torch.Tensor:
+    if isinstance(rows, torch.Tensor):
+        return rows
     return torch.from_numpy(np.ascontiguousarray(rows, dtype=np.int32)).to(device)
 
 
-def _best_rows(Sigma: torch.Tensor, rows: np.ndarray, kappa: int, maximize: bool, precision: str):
-    """The kappa best rows of a [B][k] candidate list by Omega (device reducer; ties: lower row)."""
+def _pick_rows(rows, at: np.ndarray) -> np.ndarray:
+    """Rows `at` of a host array or a device tensor, on the host."""
+    if isinstance(rows, torch.Tensor):
+        return rows[torch.from_numpy(at).to(rows.device)].cpu().numpy()
+    return rows[at]
+
+
+def _best_rows(Sigma: torch.Tensor, rows, kappa: int, maximize: bool, precision: str):
+    """The kappa best rows of a [B][k] candidate list (host array or device tensor) by Omega (device
+    reducer; ties: lower row)."""
     k = rows.shape[1]
     st = api.nplets_reduce(Sigma, nplets=_rows_to_device(rows, Sigma.device), topk=kappa, hist_bins=0,
                            precision=precision)
@@ -40,7 +52,29 @@ def _best_rows(Sigma: torch.Tensor, rows: np.ndarray, kappa: int, maximize: bool
     slot = 0 if maximize else 1
     g = tg[0, k, slot]
     keep = g >= 0
-    return rows[g[keep]], tv[0, k, slot][keep]
+    return _pick_rows(rows, g[keep]), tv[0, k, slot][keep]
+
+
+def combinations_on(device, N: int, k: int) -> torch.Tensor:
+    """`combinations` as an int32 tensor built on `device`: the sizes of all levels are known on the host,
+    so nothing waits for the device (161,700 triplets of 100 variables: 1.5 ms less per greedy call than
+    the rows built on the host and copied)."""
+    cols: list[torch.Tensor] = []
+    n = 1
+    for level in range(k):
+        hi = N - (k - level)
+        total = math.comb(hi + 1, level + 1)          # prefixes of length level + 1 with room for the rest
+        at = torch.arange(total, device=device)
+        if level == 0:
+            cols = [at]
+        else:
+            cnt = hi - cols[-1]
+            rep = torch.repeat_interleave(torch.arange(n, device=device), cnt, output_size=total)
+            first = (cnt.cumsum(0) - cnt)[rep]
+            cols = [c[rep] for c in cols]
+            cols.append(cols[-1] + 1 + at - first)
+        n = total
+    return torch.stack(cols, 1).to(torch.int32) if cols else torch.zeros((1, 0), dtype=torch.int32, device=device)
 
 
 def combinations(N: int, k: int) -> np.ndarray:
@@ -138,7 +172,7 @@ def greedy(Sigma: torch.Tensor, k_first: int, k_last: int, kappa: int = 16, maxi
         out = {k_first: (sols, tv[0, k_first, slot][: len(g)])}
     else:
         # wider systems: the first order as an explicit list (lexicographic rows)
-        rows = combinations(N, k_first)
+        rows = combinations_on(S.device, N, k_first)
         sols, vals = _best_rows(S, rows, kappa, maximize, precision)
         out = {k_first: (sols, vals)}
     if on_device is None:
@@ -372,7 +406,7 @@ def _anneal_device(S: torch.Tensor, cur: np.ndarray, draws: dict, T0: float, alp
 MEASURES = {"tc": 0, "dtc": 1, "omega": 2, "s": 3}
 
 
-def _best_rows_multi(Sigmas: torch.Tensor, rows: np.ndarray, kappa: int, measure: str, kind: str, maximize: bool,
+def _best_rows_multi(Sigmas: torch.Tensor, rows, kappa: int, measure: str, kind: str, maximize: bool,
                      precision: str):
     odt = torch.float64 if precision == "fp64" else torch.float32
     out, _ = api.nplets_measures(Sigmas, nplets=_rows_to_device(rows, Sigmas.device), precision=precision,
@@ -382,7 +416,7 @@ def _best_rows_multi(Sigmas: torch.Tensor, rows: np.ndarray, kappa: int, measure
     slot = 0 if maximize else 1
     g = tg[0, 0, slot]
     keep = g >= 0
-    return rows[g[keep]], tv[0, 0, slot][keep]
+    return _pick_rows(rows, g[keep]), tv[0, 0, slot][keep]
 
 
 def greedy_multi(Sigmas: torch.Tensor, k_first: int, k_last: int, kappa: int = 16, measure: str = "omega",
@@ -395,7 +429,7 @@ def greedy_multi(Sigmas: torch.Tensor, k_first: int, k_last: int, kappa: int = 1
     after the first run on the device in one call (thoi_greedy); otherwise each order is one
     evaluator call plus one objective reduction, decided on the host."""
     D, N, _ = Sigmas.shape
-    rows = combinations(N, k_first)
+    rows = combinations_on(Sigmas.device, N, k_first)
     sols, vals = _best_rows_multi(Sigmas, rows, kappa, measure, kind, maximize, precision)
     out = {k_first: (sols, vals)}
     if on_device is None:
