@@ -1,11 +1,15 @@
-// Subset-table ("cube") engine: FP64 streaming reductions over whole orders of 21..30 variables.
+// Subset-table ("cube") engine: streaming reductions over whole orders of many variables (FP64: 21..30,
+// FP32 with refinement: 26..30).
 //
 // An exhaustive enumeration meets every subset of S as an n-plet of its own, so the leave-one-out
 // determinants need no inverse: with ld(S) = log det R_S in a table over all 2^N subsets,
 //   log a_j = log (R_S^-1)_jj = ld(S \ j) - ld(S)
 // (the cofactor identity), and an n-plet costs one pivot and k table reads instead of a factorisation
 // and an inversion of order k ("The combinatorial explosion": the number of subsets stays, the k^3
-// per subset goes).
+// per subset goes).  A reduction needs the value itself of few n-plets, so the table (FP64 for either
+// precision) only filters: an n-plet whose bin is certain and which cannot enter a list is counted, the
+// rest is evaluated as the lane and pair engines do (nplets_cube_verify.hip), and the results are theirs
+// bit for bit.
 //
 // A subset is a prefix P (of the first h = N - 10 variables) and one of the 1024 subsets of the last
 // ten; row P of the table holds the latter ordered by size and, within a size, lexicographically.
@@ -13,15 +17,16 @@
 //    variables (right-looking, one matrix row per lane), then every lane eliminates its subset of the
 //    first six variables from its own copy of the 10 x 10 Schur complement and walks the 16 subsets
 //    of the last four.  ld of a subset is ld of the subset without its last variable plus the log of
-//    the pivot, in ascending order of the variables whatever the split, so exchangeable n-plets (equal
-//    sub-matrices) get equal values and ties stay ordered by index.
-//  - k_cube_reduce, one wavefront per (row, size): the n-plets P + (subsets of one size) have
+//    the pivot.
+//  - k_cube_filter, one wavefront per (row, size): the n-plets P + (subsets of one size) have
 //    consecutive global indices and read consecutive entries of the rows of P without one member;
 //    removing one of the ten variables stays inside the row (a table of neighbours in LDS).
-// Bound by the latency and bandwidth of the table reads (k + 1 of 8 bytes per n-plet; 67% of the wave
-// cycles wait).  N = 25, orders 3..25, top-100 and 256 bins: 4.7 ms with a factorisation per n-plet and
-// prefix sharing, 1.2 ms so (build 0.27, bounds 0.09, reduction 0.84); with the orders one after the
-// other in the grid, instead of all orders of a chunk of rows together, the reduction took 1.46 ms.
+// Bound by VALU issue (57% busy) and the latency of the table reads (k + 1 of 8 bytes per n-plet).  A
+// factorisation per n-plet against the table, top-100 and 256 bins, orders 3..N:
+//   N = 30  FP32 + refinement 66.2 / 31.7 ms (build 8, filter 23, open n-plets 2)   FP64 424 / 34.6 ms
+//   N = 27  FP32 + refinement 7.74 / 4.24 ms      N = 25  FP64 4.75 / 1.62 ms      N = 22  FP64 1.66 / 0.48 ms
+// Taking the table's values themselves (no second evaluation) measured 1.05 ms at N = 25, with errors
+// against 64-bit references of 1e-14 instead of 2e-15.
 #include "nplets_cube.hpp"
 #include "radix_pick.hpp"
 
@@ -30,6 +35,7 @@ namespace {
 
 constexpr int kBuildThreads = 256;                    // four rows
 constexpr int kBuildWaves = kBuildThreads / 64;
+constexpr int kBuildRows = 4;                         // rows per wavefront (one staging of the matrix)
 constexpr int kCubePrefix = kCubeMaxN - kCubeSuffix;  // largest prefix (20)
 constexpr int kTri10 = kCubeSuffix * (kCubeSuffix + 1) / 2;
 
@@ -98,6 +104,37 @@ __device__ __forceinline__ double fast_rcp(double x)
     return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
 }
 
+// log x for a pivot x (in (0, 1] up to rounding); NaN for x <= 0.  x = m 2^e with m in [sqrt(1/2),
+// sqrt(2)), log m = 2 atanh(s) with s = (m - 1) / (m + 1), |s| < 0.1716: the series to s^21 leaves less
+// than 1e-18 relative, and m - 1 is exact, so pivots close to 1 keep their relative accuracy.  21 of
+// the library's logarithms were a third of the row's instructions.
+__device__ __forceinline__ double pivot_log(double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    e -= low ? 1 : 0;
+    const double f = m - 1.0, den = m + 1.0, r = fast_rcp(den);
+    double s = f * r;
+    s = __builtin_fma(__builtin_fma(-den, s, f), r, s);   // the quotient's last bit
+    const double z = s * s;
+    double p = 1.0 / 21;
+    p = __builtin_fma(p, z, 1.0 / 19);
+    p = __builtin_fma(p, z, 1.0 / 17);
+    p = __builtin_fma(p, z, 1.0 / 15);
+    p = __builtin_fma(p, z, 1.0 / 13);
+    p = __builtin_fma(p, z, 1.0 / 11);
+    p = __builtin_fma(p, z, 1.0 / 9);
+    p = __builtin_fma(p, z, 1.0 / 7);
+    p = __builtin_fma(p, z, 1.0 / 5);
+    p = __builtin_fma(p, z, 1.0 / 3);
+    const double s2 = s + s;
+    const double lm = __builtin_fma(s2 * z, p, s2);
+    const double y = __builtin_fma((double)e, kLn2, lm);
+    return x > 0.0 ? y : __builtin_nan("");
+}
+
 // Subsets of suffix variables V..9 over the Schur complement s (lower triangle of variables V..9,
 // row i - V): ld of every one into row[position], starting from ld and the subset m of the variables
 // below V.
@@ -119,12 +156,13 @@ __device__ __forceinline__ void cube_walk(const double (&s)[(kCubeSuffix - V) * 
             const double t = s[tri(I, 0)] * inv;
             sfor<1, I + 1>([&](auto J) { y[tri(I - 1, J - 1)] = __builtin_fma(-t, s[tri(J, 0)], s[tri(I, J)]); });
         });
-        cube_walk<V + 1>(y, ld + log(p), m | (1 << V), row, spos);
+        cube_walk<V + 1>(y, ld + pivot_log(p), m | (1 << V), row, spos);
     }
 }
 
-// grid (ceil(2^h / 4), datasets of the group), block kBuildThreads: row P of the table of dataset
-// d0 + blockIdx.y.  Bit h - 1 - v of P is variable v.  Rows with more than kmax members are not needed.
+// grid (ceil(2^h / 16), datasets of the group), block kBuildThreads: rows P of the table of dataset
+// d0 + blockIdx.y, kBuildRows per wavefront.  Bit h - 1 - v of P is variable v.  Rows with more than kmax
+// members are not needed.
 __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __restrict__ Sigma, int N, int64_t d0,
                                                               int kmax, double* __restrict__ table)
 {
@@ -141,9 +179,6 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
     for (int i = threadIdx.x; i < kCubeRow; i += kBuildThreads) spos[i] = kSuffix.pos[i];
     stage_corr<double>(Sigma + d * N * N, N, sR, sIsd, sLogd);
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t P = __builtin_amdgcn_readfirstlane(blockIdx.x * kBuildWaves + wv);
-    const int p = __popc(P);
-    if ((P >> h) != 0 || p > kmax) return;                             // no block barrier below
     double* srow = srow_w + wv * kCubeRow;
     double* scol = scol_w + wv * 64;
     double* ssch = ssch_w + wv * 56;
@@ -151,85 +186,91 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
     // entry against suffix variable m; r[10 + q]: against member q.
     const bool suf = lane < kCubeSuffix;
     const int q = lane - kCubeSuffix;
-    uint32_t m = P;
-    int var = suf ? h + lane : 0;
-    double r[kCubeSuffix + kCubePrefix];
-    const bool row_on = suf || q < p;
-    for (int e = 0; e < p; ++e) {
-        const int v = h - 1 - (31 - __builtin_clz(m));
-        m &= ~(0x80000000u >> __builtin_clz(m));
-        if (q == e) var = v;
-    }
-    sfor<0, kCubeSuffix>([&](auto M) {
-        constexpr int c = M;
-        r[c] = suf ? sR[var * N + h + c] : 0.0;
-    });
-    m = P;
-    sfor<0, kCubePrefix>([&](auto Q) {
-        constexpr int c = Q;
-        r[kCubeSuffix + c] = 0.0;
-        if (c < p) {
+    for (int it = 0; it < kBuildRows; ++it) {                          // no block barrier below
+        const uint32_t P = __builtin_amdgcn_readfirstlane((blockIdx.x * kBuildRows + it) * kBuildWaves + wv);
+        const int p = __popc(P);
+        if ((P >> h) != 0 || p > kmax) continue;
+        uint32_t m = P;
+        int var = suf ? h + lane : 0;
+        double r[kCubeSuffix + kCubePrefix];
+        const bool row_on = suf || q < p;
+        for (int e = 0; e < p; ++e) {
             const int v = h - 1 - (31 - __builtin_clz(m));
             m &= ~(0x80000000u >> __builtin_clz(m));
-            r[kCubeSuffix + c] = row_on ? sR[var * N + v] : 0.0;
+            if (q == e) var = v;
         }
-    });
-    // eliminate the members of P one after the other
-    double piv = 1.0;
-    sfor<0, kCubePrefix>([&](auto J) {
-        constexpr int j = J;
-        if (j < p) {
-            double* cl = scol + (j & 1) * 32;
-            if (lane < 32) cl[lane] = r[kCubeSuffix + j];
-            cube_wave_sync();
-            const double pj = cl[kCubeSuffix + j];
-            piv = q == j ? pj : piv;
-            const double t = r[kCubeSuffix + j] * fast_rcp(pj);
-            sfor<j + 1, kCubePrefix>([&](auto Q) {
-                constexpr int c = Q;
-                if (c < p) r[kCubeSuffix + c] = __builtin_fma(-t, cl[kCubeSuffix + c], r[kCubeSuffix + c]);
-            });
-            sfor<0, kCubeSuffix>([&](auto M) { r[M] = __builtin_fma(-t, cl[M], r[M]); });
-        }
-    });
-    const double lp = log(piv);
-    double ld = 0.0;
-    for (int e = 0; e < p; ++e) ld += __shfl(lp, kCubeSuffix + e, 64);
-    // the Schur complement of the ten variables in every lane
-    if (suf) {
         sfor<0, kCubeSuffix>([&](auto M) {
             constexpr int c = M;
-            if (c <= lane) ssch[lane * (lane + 1) / 2 + c] = r[c];
+            r[c] = suf ? sR[var * N + h + c] : 0.0;
         });
-    }
-    cube_wave_sync();
-    double s[kTri10];
-    sfor<0, kTri10>([&](auto E) { s[E] = ssch[E]; });
-    sfor<0, 6>([&](auto T) {
-        constexpr int t = T;
-        if ((lane >> t) & 1) {
-            const double pt = s[tri(t, t)], inv = fast_rcp(pt);
-            ld += log(pt);
-            sfor<t + 1, kCubeSuffix>([&](auto I) {
-                constexpr int i = I;
-                const double f = s[tri(i, t)] * inv;
-                sfor<t + 1, i + 1>([&](auto Jc) {
-                    constexpr int c = Jc;
-                    s[tri(i, c)] = __builtin_fma(-f, s[tri(c, t)], s[tri(i, c)]);
+        m = P;
+        sfor<0, kCubePrefix>([&](auto Q) {
+            constexpr int c = Q;
+            r[kCubeSuffix + c] = 0.0;
+            if (c < p) {
+                const int v = h - 1 - (31 - __builtin_clz(m));
+                m &= ~(0x80000000u >> __builtin_clz(m));
+                r[kCubeSuffix + c] = row_on ? sR[var * N + v] : 0.0;
+            }
+        });
+        // eliminate the members of P one after the other
+        double piv = 1.0;
+        sfor<0, kCubePrefix>([&](auto J) {
+            constexpr int j = J;
+            if (j < p) {
+                double* cl = scol + (j & 1) * 32;
+                if (lane < 32) cl[lane] = r[kCubeSuffix + j];
+                cube_wave_sync();
+                const double pj = cl[kCubeSuffix + j];
+                piv = q == j ? pj : piv;
+                const double t = r[kCubeSuffix + j] * fast_rcp(pj);
+                sfor<j + 1, kCubePrefix>([&](auto Q) {
+                    constexpr int c = Q;
+                    if (c < p) r[kCubeSuffix + c] = __builtin_fma(-t, cl[kCubeSuffix + c], r[kCubeSuffix + c]);
                 });
+                sfor<0, kCubeSuffix>([&](auto M) { r[M] = __builtin_fma(-t, cl[M], r[M]); });
+            }
+        });
+        const double lp = pivot_log(piv);
+        double ld = 0.0;
+        for (int e = 0; e < p; ++e) ld += __shfl(lp, kCubeSuffix + e, 64);
+        // the Schur complement of the ten variables in every lane
+        if (suf) {
+            sfor<0, kCubeSuffix>([&](auto M) {
+                constexpr int c = M;
+                if (c <= lane) ssch[lane * (lane + 1) / 2 + c] = r[c];
             });
         }
-    });
-    double s4[11];
-    sfor<0, 4>([&](auto I) {
-        sfor<0, I + 1>([&](auto J) { s4[tri(I, J)] = s[tri(I + 6, J + 6)]; });
-    });
-    cube_walk<6>(s4, ld, lane, srow, spos);
-    cube_wave_sync();
-    // sizes up to kmax - p are needed, a prefix of the row
-    const int need = kmax - p >= kCubeSuffix ? kCubeRow : kSuffix.off[kmax - p + 1];
-    double* out = table + ((int64_t)blockIdx.y << N) + ((int64_t)P << kCubeSuffix);
-    for (int i = lane; i < need; i += 64) out[i] = srow[i];
+        cube_wave_sync();
+        double s[kTri10];
+        sfor<0, kTri10>([&](auto E) { s[E] = ssch[E]; });
+        sfor<0, 6>([&](auto T) {
+            constexpr int t = T;
+            if ((lane >> t) & 1) {
+                const double pt = s[tri(t, t)], inv = fast_rcp(pt);
+                ld += pivot_log(pt);
+                sfor<t + 1, kCubeSuffix>([&](auto I) {
+                    constexpr int i = I;
+                    const double f = s[tri(i, t)] * inv;
+                    sfor<t + 1, i + 1>([&](auto Jc) {
+                        constexpr int c = Jc;
+                        s[tri(i, c)] = __builtin_fma(-f, s[tri(c, t)], s[tri(i, c)]);
+                    });
+                });
+            }
+        });
+        double s4[11];
+        sfor<0, 4>([&](auto I) {
+            sfor<0, I + 1>([&](auto J) { s4[tri(I, J)] = s[tri(I + 6, J + 6)]; });
+        });
+        cube_walk<6>(s4, ld, lane, srow, spos);
+        cube_wave_sync();
+        // sizes up to kmax - p are needed, a prefix of the row
+        const int need = kmax - p >= kCubeSuffix ? kCubeRow : kSuffix.off[kmax - p + 1];
+        double* out = table + ((int64_t)blockIdx.y << N) + ((int64_t)P << kCubeSuffix);
+        for (int i = lane; i < need; i += 64) out[i] = srow[i];
+        cube_wave_sync();                                              // srow and the buffers are reused
+    }
 }
 
 size_t build_lds_bytes(int N)
@@ -237,56 +278,121 @@ size_t build_lds_bytes(int N)
     return ((size_t)N * N + 2 * N + kBuildWaves * (kCubeRow + 64 + 56)) * 8 + kCubeRow * 2;
 }
 
-// The orders of a call: block (chunk c, order i) of the reduction takes order p[i].k of the rows
-// [c * per, (c + 1) * per).
-struct CubePiece {
-    int32_t k, pad;
-    int64_t pos0;                                      // position of the order's first n-plet
-};
-struct CubeTable {
-    int32_t n, per, chunks, pad;
-    CubePiece p[kCubeMaxN + 1];
-};
+constexpr int kCubeWide = 2;                           // entries per lane of the reduction
 
-// sum_j (ld(S \ j) - ld(S)) of entry e of row P (size b, len entries of that size), j ascending: the
-// members of P (uniform in the wavefront), eight reads in flight, then the b members among the ten,
-// whose positions in the row are nb[0], nb[len], ...
-__device__ __forceinline__ double cube_leave_one_out(const double* __restrict__ T, uint32_t P, int b, int len, int e,
-                                                     double t0, const uint16_t* nb)
+// W consecutive entries of a row; 8-byte aligned.
+template <int W>
+struct Entries {
+    double v[W];
+};
+template <int W>
+__device__ __forceinline__ Entries<W> load_entries(const double* __restrict__ p)
 {
-    double sa = 0.0;
+    typedef double Pack __attribute__((ext_vector_type(W), aligned(8)));
+    const Pack x = *reinterpret_cast<const Pack*>(p);
+    Entries<W> r;
+#pragma unroll
+    for (int w = 0; w < W; ++w) r.v[w] = x[w];
+    return r;
+}
+
+// sa[w] = sum_j (ld(S \ j) - ld(S)) of entries e .. e + W - 1 of row P (all of size b; len entries of
+// that size, the lane's first at index i among them), j ascending: the members of P (uniform in the
+// wavefront), eight reads in flight, then the b members among the ten, whose positions in the row are
+// nb[i], nb[len + i], ... (entries past the run repeat its last: their sums are not used).  Also mx[w] =
+// max_j of the differences (log of the largest VIF) and ex[w] = sum_j of their exponentials (the sum of
+// the VIFs).
+template <int W>
+__device__ __forceinline__ void cube_leave_one_out(const double* __restrict__ T, uint32_t P, int b, int len, int e, int i,
+                                                   const Entries<W>& t0, const uint16_t* nb, double (&sa)[W],
+                                                   float (&mx)[W], float (&ex)[W])
+{
+    constexpr float kLog2e = 1.442695041f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { sa[w] = 0.0; mx[w] = 0.0f; ex[w] = 0.0f; }
+    auto add = [&](int w, double diff) {
+        sa[w] += diff;
+        const float x = (float)diff;
+        mx[w] = x > mx[w] ? x : mx[w];
+        ex[w] += __builtin_amdgcn_exp2f(x * kLog2e);
+    };
     uint32_t m = P;
     while (m) {
-        double v[8];
+        Entries<W> v[8];
         uint32_t mm = m;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             v[u] = t0;
             if (mm) {
                 const uint32_t bit = 0x80000000u >> __builtin_clz(mm);
-                v[u] = T[((int64_t)(P ^ bit) << kCubeSuffix) + e];
+                v[u] = load_entries<W>(T + ((int64_t)(P ^ bit) << kCubeSuffix) + e);
                 mm ^= bit;
             }
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (m) {
-                sa += v[u] - t0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) add(w, v[u].v[w] - t0.v[w]);
                 m ^= 0x80000000u >> __builtin_clz(m);
             }
     }
     const double* row = T + ((int64_t)P << kCubeSuffix);
+    int at_i[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) at_i[w] = i + w < len ? i + w : len - 1;
     for (int t = 0; t < b; t += 5) {
-        int at[5];
-        double v[5];
+        int at[5][W];
+        double v[5][W];
 #pragma unroll
-        for (int u = 0; u < 5; ++u) at[u] = nb[(t + u < b ? t + u : b - 1) * len];
+        for (int u = 0; u < 5; ++u)
 #pragma unroll
-        for (int u = 0; u < 5; ++u) v[u] = row[at[u]];
+            for (int w = 0; w < W; ++w) at[u][w] = nb[(t + u < b ? t + u : b - 1) * len + at_i[w]];
 #pragma unroll
-        for (int u = 0; u < 5; ++u) sa += t + u < b ? v[u] - t0 : 0.0;
+        for (int u = 0; u < 5; ++u)
+#pragma unroll
+            for (int w = 0; w < W; ++w) v[u][w] = row[at[u][w]];
+#pragma unroll
+        for (int u = 0; u < 5; ++u)
+            if (t + u < b) {                                           // uniform
+#pragma unroll
+                for (int w = 0; w < W; ++w) add(w, v[u][w] - t0.v[w]);
+            }
     }
-    return sa;
+}
+
+// How far Omega and the VIFs of a factorisation per n-plet (FP32 or FP64) may be from the table's.  With
+// E the perturbation of R_S by rounding it and factoring it (entries of a few units u = 2^-24 or 2^-53),
+// log det moves by tr(R_S^-1 E) and log a_j by (R_S^-1 E R_S^-1)_jj / a_j, to first order; |R_S^-1|_ij
+// <= sqrt(a_i a_j), so both are at most |E| (sum sqrt a)^2 <= |E| k sum a.  Taken: 4 u k sum_j a_j in FP32
+// (about 200 times what the engines differ by on the test systems) and 64 u k sum_j a_j in FP64, where a
+// wide margin costs nothing, plus the rounding of the measures.
+struct Margin {
+    double rel;              // of log det, log a_j, and relative of a_j
+    double round;
+    int vif;                 // FP32: 0 below the refinement threshold, 1 may be on either side, 2 above
+    __device__ __forceinline__ double value(double TC, double DTC) const
+    {
+        return rel + round * (fabs(TC) + fabs(DTC) + 1.0);
+    }
+};
+template <bool F32>
+__device__ __forceinline__ Margin margin_of(int k, float mx, float ex, float tau)
+{
+    Margin m;
+    if constexpr (F32) {
+        const float rel = 4.0f * 5.9604645e-8f * (float)k * ex;
+        const float v = __builtin_amdgcn_exp2f(mx * 1.442695041f), d = rel + 1e-5f;
+        m.rel = (double)rel;
+        m.round = 2.4e-7;
+        m.vif = !(v * (1.0f + d) < tau) ? (v > tau * (1.0f + d) ? 2 : 1) : 0;
+        if (!(rel < 0.25f)) m.vif = m.vif == 0 ? 1 : m.vif;
+    } else {
+        m.rel = 64.0 * 1.1102230246251565e-16 * k * (double)ex;
+        m.round = 4e-15;
+        m.vif = 0;
+    }
+    return m;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -306,6 +412,9 @@ constexpr uint32_t kSamplePieces = kSampleThreads / 64 * kSamplePer * kSampleGro
 constexpr uint32_t kSampleMin = kSamplePieces * 64;
 
 // grid (kSampleGroups, orders, datasets of the group): sbound[dataset of the group][order][group][2].
+// The values are taken at the unfavourable end of what the factorisation may make of them; FP32:
+// n-plets near or above the refinement threshold are left out.
+template <bool F32>
 __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, CubeTable tab, int K, int64_t d0,
                                                                 const double* __restrict__ table,
                                                                 uint64_t* __restrict__ sbound)
@@ -330,7 +439,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
     if (tid == 0) bias_for(a.bias, k, sbias[0], sbias[1], sbias[2]);
     __syncthreads();
     const double* T = table + ((int64_t)blockIdx.z << N);
-    double om[kSamplePer];
+    double om[kSamplePer], mu[kSamplePer];
     int nv = 0;
 #pragma unroll
     for (int u = 0; u < kSamplePer; ++u) {
@@ -356,10 +465,16 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
         const int i = (kSuffix.pos[B] - o0) / 64 * 64 + lane;
         const bool on = i < len;
         const int e = o0 + (on ? i : 0);
-        const double t0 = T[((int64_t)P << kCubeSuffix) + e];
-        const double sa = cube_leave_one_out(T, P, b, len, e, t0, snbr + kSuffix.noff[b] + (on ? i : 0));
+        const Entries<1> ld = load_entries<1>(T + ((int64_t)P << kCubeSuffix) + e);
+        double sum[1];
+        float mx[1], ex[1];
+        cube_leave_one_out<1>(T, P, b, len, e, on ? i : 0, ld, snbr + kSuffix.noff[b], sum, mx, ex);
+        const double t0 = ld.v[0], sa = sum[0];
         const double TC = -0.5 * t0 + sbias[0], DTC = 0.5 * (t0 + sa) + sbias[1];
         om[u] = on && isfinite(t0) && isfinite(sa) ? TC - DTC : __builtin_nan("");
+        const Margin mg = margin_of<F32>(k, mx[0], ex[0], a.vif_tau);
+        mu[u] = mg.value(TC, DTC);
+        if (mg.vif != 0 || !isfinite(mu[u])) om[u] = __builtin_nan("");
     }
 #pragma unroll
     for (int u = 0; u < kSamplePer; ++u) nv += __syncthreads_count(!isnan(om[u]));
@@ -374,7 +489,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
                 const uint32_t pre = sprefix;
 #pragma unroll
                 for (int u = 0; u < kSamplePer; ++u) {
-                    const uint32_t hw = (uint32_t)(red_list_key(l, om[u]) >> 32);
+                    const uint32_t hw = (uint32_t)(red_list_key(l, l == 0 ? om[u] - mu[u] : om[u] + mu[u]) >> 32);
                     if (!isnan(om[u]) && radix_match(hw, pre, pass)) atomicAdd(&rh[(hw >> (8 * pass)) & 255u], 1u);
                 }
                 __syncthreads();
@@ -400,11 +515,34 @@ __global__ void k_cube_bounds(CubeTable tab, RedArgs red, int64_t d0, const uint
         atomicMax(red.bound + ((d0 + blockIdx.y) * (red.kmax + 1) + tab.p[blockIdx.x].k) * 2 + l, (unsigned long long)~worst);
 }
 
-// grid (8 ceil(chunks / 8) orders, datasets of the group), block 256.
-__global__ __launch_bounds__(256) void k_cube_reduce(EvalArgs a, CubeTable tab, RedArgs red, int64_t d0,
+constexpr int kOpenBuf = 256;                          // open n-plets a wavefront collects in LDS
+
+// Whole wavefront: append buf[0..n) to the open list of order k.
+__device__ __forceinline__ void flush_open(const CubeOpen& o, int k, const uint32_t* buf, int n, int lane)
+{
+    if (n == 0) return;
+    cube_wave_sync();
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&o.cnt[k], (uint32_t)n);
+    at = __shfl(at, 0, 64);
+    for (int i = lane; i < n; i += 64) o.list[o.off[k] + at + i] = buf[i];
+    cube_wave_sync();
+}
+
+// grid (8 ceil(chunks / 8) orders), block 256: dataset d0, its table.
+//
+// The results are those of one factorisation per n-plet bit for bit (list values and indices, counts,
+// what is refined), so the table's values only decide where the factorisation's cannot differ: an n-plet
+// whose bin is the same over the whole margin and which cannot enter a list is counted; FP32: one above
+// the refinement threshold is queued for it; the rest (FP32: about 1%; FP64: what may enter the lists) is
+// left open and evaluated by k_cube_verify.
+template <bool F32>
+__global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, RedArgs red, CubeOpen opn, int64_t d0,
                                                      const double* __restrict__ table)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t sopen[4 * kOpenBuf];
+    __shared__ uint16_t smask[kCubeRow];
     __shared__ double sbias[3];
     const int N = a.N, h = N - kCubeSuffix;
     // all orders of one chunk of rows run together on one XCD (workgroups are dealt to the 8 XCDs
@@ -414,19 +552,32 @@ __global__ __launch_bounds__(256) void k_cube_reduce(EvalArgs a, CubeTable tab, 
     const CubePiece pc = tab.p[loc % tab.n];
     if (chunk >= tab.chunks) return;                                   // uniform
     const int k = pc.k;
-    const int64_t d = d0 + blockIdx.y;
+    const int64_t d = d0;
     uint16_t* snbr = reinterpret_cast<uint16_t*>(smem);                // [5120]
     uint32_t* sbin = reinterpret_cast<uint32_t*>(snbr + kCubeSuffix * kCubeRow / 2);   // C(n, m), n < N, m <= k
     const size_t off = (kCubeSuffix * kCubeRow + (size_t)kCubeMaxN * (kCubeMaxN + 1) * 4 + 15) / 16 * 16;
-    RedLds S = red_view(smem + off, red.topk, red.bins);
+    RedLds S = red_view(smem + off, 0, red.bins);
     for (int i = threadIdx.x; i < kCubeSuffix * kCubeRow / 2; i += 256) snbr[i] = kSuffix.nbr[i];
+    for (int i = threadIdx.x; i < kCubeRow; i += 256) smask[i] = kSuffix.mask[i];
     for (int i = threadIdx.x; i < N * (k + 1); i += 256) sbin[i] = (uint32_t)kPascal.v[i / (k + 1)][i % (k + 1)];
     if (threadIdx.x == 0) bias_for(a.bias, k, sbias[0], sbias[1], sbias[2]);
-    red_begin(S, red, (int)d, k);                                      // ends with a barrier
+    const double lo = red.lo[k], scale = (double)red.bins / (red.hi[k] - red.lo[k]);
+    double top = -__builtin_inf(), bottom = __builtin_inf();
+    RedArgs hist = red;                                                // counts only: the lists are k_cube_verify's
+    hist.topk = 0;
+    red_begin(S, hist, (int)d, k);                                     // ends with a barrier
+    if (red.topk > 0) {
+        // Omega from which the lists may take a value (every value without a bound)
+        const unsigned long long* bd = red.bound + (d * (red.kmax + 1) + k) * 2;
+        if (bd[0]) top = red_list_val(0, ~(uint64_t)bd[0]);
+        if (bd[1]) bottom = red_list_val(1, ~(uint64_t)bd[1]);
+    }
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const double* T = table + ((int64_t)blockIdx.y << N);
+    uint32_t* sbuf = sopen + wv * kOpenBuf;
+    int nbuf = 0;                                                      // uniform in the wavefront
+    const double* T = table;
     const uint32_t nrows = 1u << h;
-    const uint32_t r0 = (uint32_t)chunk * (uint32_t)tab.per;
+    const uint32_t r0 = (uint32_t)tab.row0 + (uint32_t)chunk * (uint32_t)tab.per;
     const uint32_t r1 = min(r0 + (uint32_t)tab.per, nrows);
     for (uint32_t Pw = r0 + wv; Pw < r1; Pw += 4) {
         const uint32_t P = __builtin_amdgcn_readfirstlane(Pw);
@@ -444,42 +595,83 @@ __global__ __launch_bounds__(256) void k_cube_reduce(EvalArgs a, CubeTable tab, 
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
         const uint32_t rank0 = (uint32_t)kPascal.v[N][k] - 1u - term;
-        for (int i0 = 0; i0 < len; i0 += 64) {
-            const int i = i0 + lane;
+        for (int i0 = 0; i0 < len; i0 += 64 * kCubeWide) {
+            const int i = i0 + lane * kCubeWide;
             const bool on = i < len;
             const int e = o0 + (on ? i : 0);
-            const double t0 = T[((int64_t)P << kCubeSuffix) + e];
-            const double sa = cube_leave_one_out(T, P, b, len, e, t0, snbr + kSuffix.noff[b] + (on ? i : 0));
-            FactorOut<double> f;
-            f.ld = t0;
-            f.sa = sa;
-            f.vmax = 1.0;
-            f.ok = true;                                               // a pivot <= 0 leaves NaN or -inf in ld
-            double omega = 0.0;
-            const int64_t pos = pc.pos0 + rank0 + i;
-            bool valid = false;
-            if (on)
-                valid = store_result<double>(a, true, (int)d, pos, k, f, 0.0, sbias[0], sbias[1], sbias[2], true, omega);
-            red_push(S, red, k, valid, omega, a.g_begin + pos);
+            const Entries<kCubeWide> ld = load_entries<kCubeWide>(T + ((int64_t)P << kCubeSuffix) + e);
+            double sa[kCubeWide];
+            float mx[kCubeWide], ex[kCubeWide];
+            cube_leave_one_out<kCubeWide>(T, P, b, len, e, on ? i : 0, ld, snbr + kSuffix.noff[b], sa, mx, ex);
+#pragma unroll
+            for (int w = 0; w < kCubeWide; ++w) {
+                const bool in = i + w < len;
+                const int64_t pos = pc.pos0 + rank0 + i + w;
+                const double TC = -0.5 * ld.v[w] + sbias[0], DTC = 0.5 * (ld.v[w] + sa[w]) + sbias[1];
+                const double v = TC - DTC;
+                const Margin mg = margin_of<F32>(k, mx[w], ex[w], a.vif_tau);
+                const bool bad = !isfinite(ld.v[w]) || !isfinite(sa[w]) || !(ex[w] < 3e38f);
+                const bool refine = F32 && in && (bad || mg.vif == 2);
+                // open: the VIF near the threshold, Omega near a bin edge or near the lists
+                bool open = in && !refine && (bad || mg.vif == 1);
+                const double mu = mg.value(TC, DTC);
+                if (red.topk > 0) open = open || (in && !refine && (v + mu >= top || v - mu <= bottom));
+                int bin = 0;
+                if (red.bins > 0) {
+                    // the place among the bins, and the margin there (with room for the rounding of
+                    // this product against the reducer's quotient)
+                    const double x = (v - lo) * scale, fx = floor(x), ms = mu * scale + 1e-9;
+                    const bool under = x < -ms, over = x > (double)red.bins + ms;
+                    bin = under ? red.bins : (over ? red.bins + 1 : (int)fx);
+                    const bool clear = under || over || (x - fx > ms && fx + 1.0 - x > ms && x > 0.0 && bin < red.bins);
+                    open = open || (in && !refine && !clear);
+                }
+                if (in && !refine && !open && red.bins > 0) atomicAdd(&S.hist[bin], 1u);
+                if (a.flags && in && !open) a.flags[d * a.B + pos] = refine ? THOI_NPLET_REFINED : 0;
+                if constexpr (F32) {
+                    const uint64_t mr = __ballot(refine);
+                    if (mr) {
+                        const int leader = __builtin_ctzll(mr);
+                        uint32_t at = 0;
+                        if (lane == leader) at = atomicAdd(&a.hdr->refine_count, (uint32_t)__popcll(mr));
+                        at = __shfl(at, leader, 64) + (uint32_t)__popcll(mr & __lanemask_lt());
+                        if (refine) {
+                            if (at < a.refine_cap) a.refine_list[at] = d * a.B + pos;
+                            else raise_status(a.hdr, THOI_EWORKSPACE);
+                        }
+                    }
+                }
+                const uint64_t mo = __ballot(open);
+                if (mo) {
+                    if (open) sbuf[nbuf + __popcll(mo & __lanemask_lt())] = (P << kCubeSuffix) | smask[o0 + i + w];
+                    nbuf += __popcll(mo);
+                }
+            }
+            // the wavefront's buffer goes out when the next iteration may not fit
+            if (nbuf > kOpenBuf - 64 * kCubeWide) {
+                flush_open(opn, k, sbuf, nbuf, lane);
+                nbuf = 0;
+            }
         }
     }
-    red_end(S, red, a.hdr, (int)d, k);
+    flush_open(opn, k, sbuf, nbuf, lane);
+    red_end(S, hist, a.hdr, (int)d, k);
 }
 
-size_t reduce_lds_bytes(const RedArgs& red)
+size_t filter_lds_bytes(const RedArgs& red)
 {
-    return (kCubeSuffix * kCubeRow + (size_t)kCubeMaxN * (kCubeMaxN + 1) * 4 + 15) / 16 * 16 + red_lds_bytes(red.topk, red.bins);
+    return (kCubeSuffix * kCubeRow + (size_t)kCubeMaxN * (kCubeMaxN + 1) * 4 + 15) / 16 * 16 + red_lds_bytes(0, red.bins);
 }
 
 // Chunks of rows: a wavefront spends about as long on the start of a (row, size) run as on two of its
-// 64-entry iterations, so the work of a call is the sum over its runs of 2 + iterations; about 128 per
-// workgroup, a power of two of at least 16 rows, at most 512 chunks (each workgroup leaves a segment to
-// merge).
-CubeTable cube_table(int N, int kmin, int kmax)
+// 64-entry iterations, so the work of a launch is the sum over its runs of 2 + iterations; about 128 per
+// workgroup, a power of two of at least 16 rows, at most kMaxChunks chunks.
+constexpr int64_t kMaxChunks = 4096;
+
+CubeTable cube_table(int N, int kmin, int kmax, int64_t rows)
 {
     CubeTable t{};
     const int h = N - kCubeSuffix;
-    const int64_t rows = int64_t(1) << h;
     int64_t pos = 0, work = 0;
     for (int k = kmin; k <= kmax; ++k) {
         for (int p = 0; p <= h; ++p) {
@@ -490,9 +682,10 @@ CubeTable cube_table(int N, int kmin, int kmax)
         t.p[t.n++] = CubePiece{k, 0, pos};
         pos += (int64_t)binom_u64(N, k);
     }
+    work = work / ((int64_t(1) << h) / rows);
     const int64_t want = work / (128 * t.n);
     int64_t chunks = 8;
-    while (chunks < want && chunks < 512) chunks *= 2;
+    while (chunks < want && chunks < kMaxChunks) chunks *= 2;
     while (rows / chunks < 16) chunks /= 2;
     t.chunks = (int32_t)chunks;
     t.per = (int32_t)(rows / chunks);
@@ -501,59 +694,125 @@ CubeTable cube_table(int N, int kmin, int kmax)
 
 int64_t cube_blocks(const CubeTable& t) { return (int64_t)(t.chunks + 7) / 8 * 8 * t.n; }
 
-}  // namespace
-
-bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_opts* opts)
-{
-    if (sel->mode != THOI_SEL_RANGE || opts->precision != THOI_FP64 || !opts->reduce || D < 1) return false;
-    // orders 1 and 2 have Omega = 0 up to rounding: their lists would be ordered by other rounding
-    if (sel->kmin < 3) return false;
-    if (opts->engine != THOI_ENGINE_AUTO || N < kCubeMinN || N > kCubeMaxN) return false;
-    // whole orders only, and enough of the subsets that the table holds
-    int64_t all = 0, need = 0;
-    for (int k = sel->kmin; k <= sel->kmax; ++k) all += (int64_t)binom_u64(N, k);
-    for (int k = 0; k <= sel->kmax; ++k) need += (int64_t)binom_u64(N, k);
-    if (sel->g_begin != 0 || sel->g_count != all) return false;
-    return sel->kmax >= 8 && all >= need / 8;
-}
-
+// Datasets whose tables are held at a time: up to 256 MB together, at least one dataset's.
 int64_t cube_group(int32_t N, int64_t D)
 {
-    // tables of up to 256 MB together, at least one dataset's
     const int64_t g = (int64_t(1) << 28) >> (N + 3);
     return g < 1 ? 1 : (g < D ? g : D);
 }
 
-size_t cube_table_bytes(int32_t N, int64_t D)
+// Rows filtered between two evaluations of the open lists, and the largest number of n-plets of order k
+// in such an aligned block of rows: the high prefix bits fix c members, the rest is free.
+constexpr int kFilterBits = 18;
+int filter_bits(int N) { return N - kCubeSuffix < kFilterBits ? N - kCubeSuffix : kFilterBits; }
+int64_t open_cap(int N, int k)
 {
-    // the tables, then the sample keys of every order
-    return (size_t)cube_group(N, D) * (((size_t)8 << N) + (size_t)(N + 1) * kSampleGroups * 16);
+    const int free_vars = filter_bits(N) + kCubeSuffix;
+    int64_t most = 0;
+    for (int c = 0; c <= N - free_vars && c <= k; ++c) {
+        const int64_t n = (int64_t)binom_u64(free_vars, k - c);
+        most = n > most ? n : most;
+    }
+    return most;
 }
 
-int64_t cube_segments(int32_t N, int kmin, int kmax)
+struct CubeMem {
+    size_t sample, cnt, list, total;                   // behind the tables
+    CubeOpen open;
+};
+CubeMem cube_mem(int N, int64_t D, int kmin, int kmax)
 {
-    return cube_blocks(cube_table(N, kmin, kmax));
+    CubeMem m{};
+    const int64_t g = cube_group(N, D);
+    size_t off = (size_t)g << (N + 3);
+    m.sample = off;
+    off = align_up(off + (size_t)g * (N + 1) * kSampleGroups * 16, 256);
+    m.cnt = off;
+    off += 256;
+    m.list = off;
+    int64_t o = 0;
+    for (int k = kmin; k <= kmax; ++k) {
+        m.open.off[k] = o;
+        o += open_cap(N, k);
+    }
+    off = align_up(off + (size_t)o * 4, 256);
+    m.total = off;
+    return m;
 }
 
-void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, double* table, hipStream_t s)
+}  // namespace
+
+int cube_kmax(bool f32, int kmax) { return f32 && kmax > kF32LaneMax ? kF32LaneMax : kmax; }
+
+bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_opts* opts)
+{
+    if (sel->mode != THOI_SEL_RANGE || !opts->reduce || D < 1) return false;
+    const bool f32 = opts->precision == THOI_FP32_REFINE;
+    if (!f32 && opts->precision != THOI_FP64) return false;
+    // orders 1 and 2 have Omega = 0 up to rounding: their lists would be ordered by other rounding
+    if (sel->kmin < 3) return false;
+    if (opts->engine != THOI_ENGINE_AUTO || N < (f32 ? kCubeMinN32 : kCubeMinN) || N > kCubeMaxN) return false;
+    // whole orders only, and enough of the subsets that the table holds
+    int64_t all = 0, need = 0;
+    for (int k = sel->kmin; k <= sel->kmax; ++k) all += (int64_t)binom_u64(N, k);
+    if (sel->g_begin != 0 || sel->g_count != all) return false;
+    const int kmax = cube_kmax(f32, sel->kmax);
+    all = 0;
+    for (int k = sel->kmin; k <= kmax; ++k) all += (int64_t)binom_u64(N, k);
+    for (int k = 0; k <= kmax; ++k) need += (int64_t)binom_u64(N, k);
+    return kmax >= (f32 ? 12 : 8) && all >= need / (f32 ? 2 : 8);
+}
+
+size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax) { return cube_mem(N, D, kmin, kmax).total; }
+
+int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax)
+{
+    const int64_t rows = int64_t(1) << (N - kCubeSuffix);
+    return (rows >> filter_bits(N)) * (kmax - kmin + 1) * kVerifyBlocks * D;
+}
+
+void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
+                 const std::function<void(hipStream_t)>& beside, hipStream_t s)
 {
     static_assert(sizeof(kSuffixHost.nbr) == kCubeSuffix * kCubeRow, "one neighbour per element");
-    const CubeTable tab = cube_table(a.N, kmin, kmax);
-    const int64_t blocks = cube_blocks(tab);
     const int64_t rows = int64_t(1) << (a.N - kCubeSuffix);
+    const int64_t step = int64_t(1) << filter_bits(a.N);
+    CubeTable tab = cube_table(a.N, kmin, kmax, step);
+    const int64_t blocks = cube_blocks(tab);
     const int64_t group = cube_group(a.N, a.D);
+    CubeMem m = cube_mem(a.N, a.D, kmin, kmax);
+    char* base = static_cast<char*>(mem);
+    double* table = static_cast<double*>(mem);
+    uint64_t* sbound = reinterpret_cast<uint64_t*>(base + m.sample);
+    m.open.list = reinterpret_cast<uint32_t*>(base + m.list);
+    m.open.cnt = reinterpret_cast<uint32_t*>(base + m.cnt);
+    const auto sample = f32 ? k_cube_sample<true> : k_cube_sample<false>;
+    const auto filter = f32 ? k_cube_filter<true> : k_cube_filter<false>;
     for (int64_t d0 = 0; d0 < a.D; d0 += group) {
         const int64_t nd = d0 + group < a.D ? group : a.D - d0;
-        hipLaunchKernelGGL(k_cube_build, dim3((unsigned)((rows + kBuildWaves - 1) / kBuildWaves), (unsigned)nd),
-                           dim3(kBuildThreads), build_lds_bytes(a.N), s, a.Sigma, a.N, d0, kmax, table);
+        {
+            const bool two = d0 == 0 && beside;
+            FanScope fan(s, two && !serial ? 2 : 1);
+            if (two) beside(fan.stream(1));
+            const int64_t nb = (rows + kBuildWaves * kBuildRows - 1) / (kBuildWaves * kBuildRows);
+            hipLaunchKernelGGL(k_cube_build, dim3((unsigned)nb, (unsigned)nd), dim3(kBuildThreads), build_lds_bytes(a.N),
+                               fan.stream(0), a.Sigma, a.N, d0, kmax, table);
+        }
         if (red.topk > 0) {
-            uint64_t* sbound = reinterpret_cast<uint64_t*>(table + (group << a.N));
-            hipLaunchKernelGGL(k_cube_sample, dim3(kSampleGroups, (unsigned)tab.n, (unsigned)nd), dim3(kSampleThreads), 0, s,
-                               a, tab, red.topk, d0, table, sbound);
+            hipLaunchKernelGGL(sample, dim3(kSampleGroups, (unsigned)tab.n, (unsigned)nd), dim3(kSampleThreads), 0, s, a, tab,
+                               red.topk, d0, table, sbound);
             hipLaunchKernelGGL(k_cube_bounds, dim3((unsigned)tab.n, (unsigned)nd), dim3(64), 0, s, tab, red, d0, sbound);
         }
-        hipLaunchKernelGGL(k_cube_reduce, dim3((unsigned)blocks, (unsigned)nd), dim3(256), reduce_lds_bytes(red), s, a, tab,
-                           red, d0, table);
+        // one dataset at a time, block of rows after block of rows
+        for (int64_t e = 0; e < nd; ++e) {
+            for (int64_t r0 = 0; r0 < rows; r0 += step) {
+                tab.row0 = (int32_t)r0;
+                ws_clear(m.open.cnt, 256, s);
+                hipLaunchKernelGGL(filter, dim3((unsigned)blocks), dim3(256), filter_lds_bytes(red), s, a, tab, red, m.open,
+                                   d0 + e, table + (e << a.N));
+                cube_verify_launch(a, tab, m.open, red, d0 + e, f32, serial, s);
+            }
+        }
     }
 }
 

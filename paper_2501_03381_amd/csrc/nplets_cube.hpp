@@ -1,5 +1,8 @@
-// Subset-table ("cube") engine of whole-order reductions: see nplets_cube.hip.
+// Subset-table ("cube") engine of whole-order reductions: see nplets_cube.hip (the table and the
+// filter) and nplets_cube_verify.hip (the n-plets the filter leaves open).
 #pragma once
+
+#include <functional>
 
 #include "nplets_fwd_common.hpp"
 
@@ -8,14 +11,42 @@ namespace thoi {
 constexpr int kCubeSuffix = 10;                       // variables of a table row
 constexpr int kCubeRow = 1 << kCubeSuffix;
 constexpr int kCubeMinN = 21, kCubeMaxN = 30;
+constexpr int kCubeMinN32 = 26;                       // FP32 + refinement
+
+// The orders of a call and the rows of one launch: block (chunk c, order i) takes order p[i].k of the
+// rows [row0 + c * per, row0 + (c + 1) * per).
+struct CubePiece {
+    int32_t k, pad;
+    int64_t pos0;                                      // position of the order's first n-plet
+};
+struct CubeTable {
+    int32_t n, per, chunks, row0;
+    CubePiece p[kCubeMaxN + 1];
+};
+
+// N-plets whose result the filter cannot tell (row of the table << 10 | subset of the last ten),
+// by order: cnt[k] of them at list + off[k].
+struct CubeOpen {
+    uint32_t* list;
+    uint32_t* cnt;                                     // [32]
+    int64_t off[kCubeMaxN + 2];
+};
+constexpr int kVerifyBlocks = 256;                     // workgroups per order and launch
 
 // Whether the library's choice for this reduction is the cube engine, workspace permitting.
 bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_opts* opts);
-// Datasets whose tables are held at a time, and the bytes of those tables.
-int64_t cube_group(int32_t N, int64_t D);
-size_t cube_table_bytes(int32_t N, int64_t D);
-// Segments the reduction of one dataset leaves (an upper bound).
-int64_t cube_segments(int32_t N, int kmin, int kmax);
-void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, double* table, hipStream_t s);
+// Largest order the cube engine takes (FP32: the lane engine's; orders above go to the pair engine).
+int cube_kmax(bool f32, int kmax);
+// Bytes behind the segments and the queue: tables, sample keys and open lists.
+size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax);
+// Segments the reduction leaves (an upper bound).
+int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax);
+// beside (or empty): launches of the call that do not touch the table, put on a stream beside the first
+// table's build.  serial: everything on s.
+void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
+                 const std::function<void(hipStream_t)>& beside, hipStream_t s);
+// The open n-plets of dataset d, evaluated as the lane and pair engines do.
+void cube_verify_launch(const EvalArgs& a, const CubeTable& tab, const CubeOpen& open, const RedArgs& red, int64_t d,
+                        bool f32, bool serial, hipStream_t s);
 
 }  // namespace thoi

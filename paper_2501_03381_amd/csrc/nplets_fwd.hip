@@ -428,7 +428,11 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         const Plan P = opts->precision == THOI_FP64 ? make_plan<double>(N, D, sel, true, opts)
                                                     : make_plan<float>(N, D, sel, true, opts);
         int64_t segs = P.seg_cap * D;
-        if (cube) segs = cube_segments(N, sel->kmin, sel->kmax) * D;
+        if (cube) {
+            const bool f32 = opts->precision != THOI_FP64;
+            // orders above the cube engine's stay with the pair engine's plan
+            segs = cube_segments(N, D, sel->kmin, cube_kmax(f32, sel->kmax)) + P.wblk * D;
+        }
         w.seg_cap = (uint32_t)(segs > 0 ? segs : 1);
         w.seg_key_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);
         w.seg_g_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);
@@ -436,7 +440,11 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         w.late_cap = w.refine_cap;
         if (w.late_cap) { w.late_off = off; off = align_up(off + (size_t)w.late_cap * sizeof(LateEntry), 256); }
     }
-    if (cube) { w.table_off = off; off = align_up(off + cube_table_bytes(N, D), 256); }
+    if (cube) {
+        const bool f32 = opts->precision != THOI_FP64;
+        w.table_off = off;
+        off = align_up(off + cube_bytes(N, D, sel->kmin, cube_kmax(f32, sel->kmax)), 256);
+    }
     w.total = off;
     return w;
 }
@@ -671,7 +679,28 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
     if (D == 0 || a.B == 0) return hip_status(hipGetLastError());
 
     if (cube) {
-        cube_launch(a, red, sel->kmin, sel->kmax, reinterpret_cast<double*>(base + w.table_off), s);
+        const bool f32 = opts->precision != THOI_FP64;
+        const int kc = cube_kmax(f32, sel->kmax);
+        // the orders above, if any, are few n-plets of the pair engine's, beside the table's build
+        std::function<void(hipStream_t)> beside;
+        if (sel->kmax > kc)
+            beside = [&](hipStream_t t) {
+                thoi_nplets hi = *sel;
+                for (int k = sel->kmin; k <= kc; ++k) {
+                    hi.g_begin += (int64_t)binom_u64(N, k);
+                    hi.g_count -= (int64_t)binom_u64(N, k);
+                }
+                Plan P = make_plan<float>(N, D, &hi, reduce, opts);
+                P.serial = true;
+                EvalArgs b = a;
+                b.g_begin = hi.g_begin;
+                if (b.flags) b.flags += hi.g_begin;
+                b.seg_tiles = P.seg_tiles;
+                b.wave_tile = P.wave_tile;
+                b.wave_tile_hi = P.wave_tile_hi;
+                launch_engines<float, THOI_SEL_RANGE>(b, P, red, t);
+            };
+        cube_launch(a, red, sel->kmin, kc, f32, serial, base + w.table_off, beside, s);
     } else if (opts->precision == THOI_FP64) {
         Plan P = make_plan<double>(N, D, sel, reduce, opts);
         P.serial = serial;

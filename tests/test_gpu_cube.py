@@ -1,7 +1,6 @@
-"""Subset-table engine of whole-order FP64 reductions (21..30 variables) against one factorisation per n-plet
-(engine="factor"): the same lists and histograms, values to 1e-9 (the FP64 tolerance of the evaluation tests).
-No value of these inputs lies within rounding of a bin edge or of another list entry, so indices and counts
-are compared exactly."""
+"""Subset-table engine of whole-order reductions (FP64: 21..30 variables, FP32 with refinement: 26..30) against
+one factorisation per n-plet (engine="factor"): the table only decides where the factorisation cannot differ,
+so values, indices, counts and flags are the same bit for bit."""
 import ctypes
 
 import numpy as np
@@ -29,8 +28,7 @@ def both(api, S, kmin, kmax, **kw):
 
 def same(a, b):
     assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
-    assert np.array_equal(np.isnan(a[0]), np.isnan(b[0]))
-    assert np.abs(np.nan_to_num(a[0]) - np.nan_to_num(b[0])).max() <= 1e-9
+    assert np.array_equal(a[0], b[0], equal_nan=True)
 
 
 # orders that start or end inside a row, a single order, every order, several datasets
@@ -88,6 +86,34 @@ def test_cube_accumulates_and_takes_the_least_workspace(env):
         assert api.device_status(ws) == B.THOI_OK
         res.append(st.result())
     same(*res)
+
+
+# FP32 with refinement: FP64 decides only where FP32 cannot differ, so everything is the lane engine's bit for bit
+@pytest.mark.parametrize("kmin,kmax,K,bins,near,sym", [
+    (3, 13, 100, 256, False, False), (3, 12, 256, 4096, True, False), (5, 26, 7, 0, False, False),
+    (3, 26, 0, 64, False, False), (4, 12, 20, 16, False, True)])
+def test_filtered_fp32_is_the_lane_engine_bit_for_bit(env, kmin, kmax, K, bins, near, sym):
+    torch, api, B, synth = env
+    N = 26
+    rng = np.random.default_rng(kmax)
+    X = synth.factor_model(rng, 2000, N, 6)
+    if near:
+        X[:, 20] = X[:, 3] + 0.03 * rng.standard_normal(2000)     # VIFs on both sides of the threshold
+    S = torch.from_numpy(np.cov(X.T)).cuda()
+    if sym:                                                       # every n-plet of an order ties
+        S = torch.full((N, N), 0.25, dtype=torch.float64, device="cuda") + 0.75 * torch.eye(N, dtype=torch.float64, device="cuda")
+    n = B.thoi_count(N, kmin, kmax)
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] fp32 cube orders {kmin}..{kmax} K={K} bins={bins} near={near} sym={sym} {e}", flush=True)
+        f = torch.full((1, n), 9, dtype=torch.uint8, device="cuda")
+        st = api.nplets_reduce(S, orders=(kmin, kmax), topk=K, hist_bins=bins, hist_range=(-7.3, 5.1), engine=e, flags=f,
+                               bias_correct=near, T=400 if near else 0, check=not near)
+        res.append(([st.top_val, st.top_g] if K else []) + ([st.hist] if bins else []) + [f])
+    for x, y in zip(*res):
+        assert torch.equal(torch.nan_to_num(x.double(), nan=77.0), torch.nan_to_num(y.double(), nan=77.0))
+    if near:
+        assert 0 < int((res[0][-1] == B.THOI_NPLET_REFINED).sum()) < n
 
 
 def test_exchangeable_variables_tie_by_index(env):
