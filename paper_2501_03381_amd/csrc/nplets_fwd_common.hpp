@@ -110,14 +110,20 @@ __device__ __forceinline__ void bias_for(const BiasParams& bp, int k, double& dt
 }
 
 // ------------------------------------------------------------------------------------------------
-// Result handling shared by the engines.  Returns whether the value may enter the reducer.
+// Result handling shared by the engines.
 // ------------------------------------------------------------------------------------------------
+// Measures of a factorisation (position o of the output); queues the n-plet for the FP64 pass where FP32
+// is not enough.
 template <typename F>
-__device__ __forceinline__ bool store_result(const EvalArgs& a, bool reduce, int d, int64_t pos, int k,
-                                             const FactorOut<F>& f, double sumlogd, double dtc, double ddtc,
-                                             double eta, bool fp64_pass, double& omega)
+struct Measured {
+    F TC, DTC, OM, SI;
+    uint8_t flag;
+    bool bad, queued;
+};
+template <typename F>
+__device__ __forceinline__ Measured<F> measure(const EvalArgs& a, int64_t o, const FactorOut<F>& f, double dtc,
+                                               double ddtc, bool fp64_pass)
 {
-    const int64_t o = (int64_t)d * a.B + pos;
     uint8_t flag = 0;
     F TC, DTC;
     const bool finite = isfinite(f.ld) && isfinite(f.sa);
@@ -150,22 +156,37 @@ __device__ __forceinline__ bool store_result(const EvalArgs& a, bool reduce, int
         TC = F(-0.5) * f.ld + (F)dtc;
         DTC = F(0.5) * (f.ld + f.sa) + (F)ddtc;
     }
-    const F OM = TC - DTC, SI = TC + DTC;
-    omega = (double)OM;
+    return Measured<F>{TC, DTC, TC - DTC, TC + DTC, flag, bad, queued};
+}
+template <typename F>
+__device__ __forceinline__ double entropy_of(int k, const FactorOut<F>& f, bool bad, double sumlogd, double eta)
+{
+    return bad ? __builtin_nan("") : 0.5 * (k * kLog2PiE + (double)f.ld + sumlogd) - eta;
+}
+
+// Returns whether the value may enter the reducer.
+template <typename F>
+__device__ __forceinline__ bool store_result(const EvalArgs& a, bool reduce, int d, int64_t pos, int k,
+                                             const FactorOut<F>& f, double sumlogd, double dtc, double ddtc,
+                                             double eta, bool fp64_pass, double& omega)
+{
+    const int64_t o = (int64_t)d * a.B + pos;
+    const Measured<F> r = measure<F>(a, o, f, dtc, ddtc, fp64_pass);
+    omega = (double)r.OM;
     if (!reduce) {
         const int64_t plane = (int64_t)a.D * a.B;
         if (a.out_f32) {
             float* op = static_cast<float*>(a.out);
-            op[o] = (float)TC; op[plane + o] = (float)DTC; op[2 * plane + o] = (float)OM; op[3 * plane + o] = (float)SI;
-            if (a.write_H) op[4 * plane + o] = bad ? __builtin_nanf("") : (float)(0.5 * (k * kLog2PiE + (double)f.ld + sumlogd) - eta);
+            op[o] = (float)r.TC; op[plane + o] = (float)r.DTC; op[2 * plane + o] = (float)r.OM; op[3 * plane + o] = (float)r.SI;
+            if (a.write_H) op[4 * plane + o] = (float)entropy_of<F>(k, f, r.bad, sumlogd, eta);
         } else {
             double* op = static_cast<double*>(a.out);
-            op[o] = (double)TC; op[plane + o] = (double)DTC; op[2 * plane + o] = (double)OM; op[3 * plane + o] = (double)SI;
-            if (a.write_H) op[4 * plane + o] = bad ? __builtin_nan("") : 0.5 * (k * kLog2PiE + (double)f.ld + sumlogd) - eta;
+            op[o] = (double)r.TC; op[plane + o] = (double)r.DTC; op[2 * plane + o] = (double)r.OM; op[3 * plane + o] = (double)r.SI;
+            if (a.write_H) op[4 * plane + o] = entropy_of<F>(k, f, r.bad, sumlogd, eta);
         }
     }
-    if (a.flags) a.flags[o] = flag;
-    return !bad && !queued;
+    if (a.flags) a.flags[o] = r.flag;
+    return !r.bad && !r.queued;
 }
 
 // ------------------------------------------------------------------------------------------------

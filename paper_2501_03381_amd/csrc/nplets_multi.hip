@@ -22,7 +22,7 @@ constexpr int kMaxClasses = 8;
 
 // n-plets per lane of a class (consecutive, one unranking then successors): several in the class
 // of the smallest orders, whose factorisation is a few dozen instructions and where the
-// unranking would otherwise dominate (FP32 six: at orders 3..5 over 1024 datasets four, six,
+// unranking would otherwise dominate (FP32, not staged, six: at orders 3..5 over 1024 datasets four, six,
 // seven and eight per lane measured 1.89, 1.67, 2.0 and 2.11 ms); elsewhere as in the
 // single-dataset engine.
 template <typename F>
@@ -167,25 +167,147 @@ __device__ __forceinline__ int64_t multi_ostart(int Nd, int kmin, int k)
     return s;
 }
 
-// Persistent launch of one register class.  grid (G), block kTile; U units in the class.
-// LDS: sR [nmax^2] F | sIsd [nmax] | sLogd [nmax] | sBin [nmax * KHI] | (reduce) RedLds
-template <typename F, int KLO, int KHI, bool RED>
-__global__ __launch_bounds__(kTile) void k_eval_multi(EvalArgs a, MultiArgs m, int cls, int64_t U, int nmax,
+// FP32 output of the class of the smallest orders ("staged"): a wavefront's 64 kStageS consecutive
+// results are collected in LDS (TC and DTC, of which Omega and S are made on the way out, the entropy and
+// the flags) and go out in rows of 64.  Bound by VALU issue (the factorisation and the successor; the
+// output alone would take 110 us).  256 datasets of 10..40 variables, orders 3..5, 44 M n-plets: stored by
+// each lane, six n-plets unrolled at 157 registers and three wavefronts per SIMD, 482 us; rows of 64 with
+// the loop rolled at 128 registers and four wavefronts 440; unranking by bisection, eight, ten, twelve and
+// fourteen n-plets per lane 317, 315, 304 and 347 (fourteen: a workgroup less per CU); three and five
+// wavefronts per SIMD 321 and 319.  Held in registers and stored in pieces of 16 bytes per lane: 571.
+template <typename F>
+__host__ __device__ constexpr bool staged_class(int khi, bool red) { return sizeof(F) == 4 && !red && khi <= 8; }
+constexpr int kStageS = 12;                                 // n-plets per lane
+constexpr int kStageW = 64 * kStageS;
+struct StageOut {
+    float* v;                        // [planes][kStageW]
+    uint8_t* flag;                   // [kStageW]
+};
+__host__ __device__ constexpr int stage_planes(bool write_H) { return write_H ? 3 : 2; }
+__host__ __device__ constexpr size_t stage_bytes(bool write_H) { return (size_t)kStageW * (4 * stage_planes(write_H) + 1); }
+// Everything a wavefront wrote to its buffer is visible to its other lanes.
+__device__ __forceinline__ void stage_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The r-th of the C(N, K) combinations in lexicographic order, the same few steps in every lane: with the
+// rank from the end R = C(N, K) - 1 - r = sum_i C(y_i, K - i), y_0 > y_1 > ..., each y_i is the largest
+// with C(y_i, K - i) <= what is left of R (found by bisection; K - i = 2 in closed form) and
+// c_i = N - 1 - y_i.  sBin: C(n, m), n < N, m < kb, kb > K; top: the largest power of two below N (1 at
+// least).
+template <int K>
+__device__ __forceinline__ void unrank_bisect(uint64_t r, int N, const uint64_t* __restrict__ sBin, int kb, int top,
+                                              int (&c)[K > 0 ? K : 1])
+{
+    if constexpr (K > 0) {
+        uint64_t R = kPascal.v[N][K] - 1 - r;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const int m = K - i;
+            if (m > 2) {
+                int y = 0;
+                for (int st = top; st > 0; st >>= 1) {
+                    const int z = y + st;
+                    if (z < N && sBin[z * kb + m] <= R) y = z;
+                }
+                R -= sBin[y * kb + m];
+                c[i] = N - 1 - y;
+            } else if (m == 2) {
+                const int q = (int)R;                      // < C(N, 2)
+                int y = (int)(0.5f * (1.0f + sqrtf((float)(8 * q + 1))));
+                y -= y * (y - 1) / 2 > q ? 1 : 0;
+                y += (y + 1) * y / 2 <= q ? 1 : 0;
+                R = (uint64_t)(q - y * (y - 1) / 2);
+                c[i] = N - 1 - y;
+            } else {
+                c[i] = N - 1 - (int)R;
+            }
+        }
+    }
+}
+
+// lane_task for kStageS consecutive n-plets of one lane into the wavefront's buffer.
+template <int K>
+__device__ __forceinline__ void staged_task(const EvalArgs& a, const LaneCtx& cx, const float* sR, const double* sLogd,
+                                            const uint64_t* sBin, int top, int64_t cnt, const StageOut& st)
+{
+    int c[K > 0 ? K : 1];
+    unrank_bisect<K>((uint64_t)cx.local, cx.N, sBin, cx.kb, top, c);
+    const int at = (threadIdx.x & 63) * kStageS;
+    const int n = cnt - cx.local < kStageS ? (int)(cnt - cx.local) : kStageS;
+#pragma unroll 1
+    for (int j = 0; j < n; ++j) {
+        if (j > 0) next_lex<K>(c, cx.N);
+        const FactorOut<float> f = lane_factor<float, K>(c, sR, cx.N);
+        const Measured<float> r = measure<float>(a, cx.pos0 + cx.local + j, f, cx.dtc, cx.ddtc, false);
+        st.v[at + j] = r.TC;
+        st.v[kStageW + at + j] = r.DTC;
+        if (a.write_H) {
+            double sumlogd = 0.0;
+#pragma unroll
+            for (int i = 0; i < K; ++i) sumlogd += sLogd[c[i]];
+            st.v[2 * kStageW + at + j] = (float)entropy_of<float>(K, f, r.bad, sumlogd, cx.eta);
+        }
+        st.flag[at + j] = r.flag;
+    }
+}
+template <int K, int KHI>
+__device__ __forceinline__ void staged_dispatch(int k, const EvalArgs& a, const LaneCtx& cx, const float* sR,
+                                                const double* sLogd, const uint64_t* sBin, int top, int64_t cnt,
+                                                const StageOut& st)
+{
+    if (k == K) staged_task<K>(a, cx, sR, sLogd, sBin, top, cnt, st);
+    else if constexpr (K < KHI) staged_dispatch<K + 1, KHI>(k, a, cx, sR, sLogd, sBin, top, cnt, st);
+}
+// The first n results of the wavefront's buffer to output positions o, o + 1, ...
+__device__ __forceinline__ void staged_store(const EvalArgs& a, int64_t o, int n, const StageOut& st)
+{
+    const int lane = threadIdx.x & 63;
+    float* p0 = static_cast<float*>(a.out) + o;
+    float* p1 = p0 + a.B;
+    float* p2 = p1 + a.B;
+    float* p3 = p2 + a.B;
+    uint8_t* pf = a.flags ? a.flags + o : nullptr;
+#pragma unroll
+    for (int j = 0; j < kStageS; ++j) {
+        const int e = 64 * j + lane;
+        if (e < n) {
+            const float TC = st.v[e], DTC = st.v[kStageW + e];
+            p0[e] = TC;
+            p1[e] = DTC;
+            p2[e] = TC - DTC;
+            p3[e] = TC + DTC;
+            if (a.write_H) p3[a.B + e] = st.v[2 * kStageW + e];
+            if (pf) pf[e] = st.flag[e];
+        }
+    }
+}
+
+// Persistent launch of one register class.  grid (G), block kTile; U units in the class.  STAGED: FP32
+// output through LDS.
+// LDS: sR [nmax^2] F | sIsd [nmax] | sLogd [nmax] | sBin [nmax * KB] | (reduce) RedLds |
+//      (STAGED) stage_bytes per wavefront
+template <typename F, int KLO, int KHI, bool RED, bool STAGED = false>
+__global__ __launch_bounds__(kTile, STAGED ? 4 : 1) void k_eval_multi(EvalArgs a, MultiArgs m, int cls, int64_t U, int nmax,
                                                       RedArgs red)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double sbias[3];
-    constexpr int S = multi_per_lane<F>(KHI);
+    constexpr int S = STAGED ? kStageS : multi_per_lane<F>(KHI);
+    constexpr int KB = STAGED ? KHI + 1 : KHI;             // binomial columns
     F* sR = reinterpret_cast<F*>(smem);
     const size_t off = ((size_t)nmax * nmax * sizeof(F) + 15) / 16 * 16;
     double* sIsd = reinterpret_cast<double*>(smem + off);
     double* sLogd = sIsd + nmax;
     uint64_t* sBin = reinterpret_cast<uint64_t*>(sLogd + nmax);
-    RedLds Rl = red_view(smem + lane_stage_bytes(nmax, KHI, sizeof(F)), red.topk, red.bins);
+    RedLds Rl = red_view(smem + lane_stage_bytes(nmax, KB, sizeof(F)), red.topk, red.bins);
     const int64_t G = gridDim.x;
     const int64_t u0 = (int64_t)blockIdx.x * U / G, u1 = ((int64_t)blockIdx.x + 1) * U / G;
     if (u0 >= u1) return;                                  // uniform
-    stage_binomials(nmax, KHI, sBin);                      // C(n, m) does not depend on the dataset
+    stage_binomials(nmax, KB, sBin);                       // C(n, m) does not depend on the dataset
     const int64_t* uo = m.t.unit_off + (int64_t)cls * (m.D + 1);
     const int64_t per_unit = m.per_unit[cls];
     const int klo = KLO > m.kmin ? KLO : m.kmin, khi = KHI < m.kmax ? KHI : m.kmax;
@@ -237,7 +359,7 @@ __global__ __launch_bounds__(kTile) void k_eval_multi(EvalArgs a, MultiArgs m, i
         cx.pos0 = m.t.out_off[d] + gbase;
         cx.gbase = gbase;
         cx.N = Nd;
-        cx.kb = KHI;
+        cx.kb = KB;
         cx.reduce = RED;
         cx.dtc = sbias[0];
         cx.ddtc = sbias[1];
@@ -245,6 +367,21 @@ __global__ __launch_bounds__(kTile) void k_eval_multi(EvalArgs a, MultiArgs m, i
         // this and the following units of the same (dataset, order) inside the range
         const int64_t run = nu - rel < u1 - u ? nu - rel : u1 - u;
         const int64_t b0 = rel * per_unit, b1 = (rel + run) * per_unit < cnt ? (rel + run) * per_unit : cnt;
+        if constexpr (STAGED) {
+            const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            unsigned char* buf = smem + lane_stage_bytes(nmax, KB, 4) + wv * stage_bytes(a.write_H);
+            const StageOut st{reinterpret_cast<float*>(buf), buf + kStageW * 4 * stage_planes(a.write_H)};
+            const int top = Nd > 1 ? 1 << (31 - __builtin_clz(Nd - 1)) : 1;
+            for (int64_t tb = b0 + 64 * S * wv; tb < b1; tb += (int64_t)kTile * S) {
+                cx.local = tb + S * (int)(threadIdx.x & 63);
+                if (cx.local < b1) staged_dispatch<KLO, KHI>(k, a, cx, sR, sLogd, sBin, top, b1, st);
+                stage_sync();
+                staged_store(a, cx.pos0 + tb, (int)(b1 - tb < 64 * S ? b1 - tb : 64 * S), st);
+                stage_sync();                              // the next round overwrites the buffer
+            }
+            u += run;
+            continue;
+        }
         for (int64_t tb = b0; tb < b1; tb += (int64_t)kTile * S) {
             cx.local = tb + (int64_t)S * threadIdx.x;
             double omega[S] = {};
@@ -341,11 +478,11 @@ __global__ __launch_bounds__(64) void k_refine_multi(EvalArgs a, MultiArgs m, in
 typedef void (*MultiKernel)(EvalArgs, MultiArgs, int, int64_t, int, RedArgs);
 
 template <typename F, bool RED>
-MultiKernel multi_kernel_r(int cls)
+MultiKernel multi_kernel_r(int cls, bool staged)
 {
     if constexpr (sizeof(F) == 4) {
         switch (cls) {
-            case 0: return k_eval_multi<F, 0, 8, RED>;
+            case 0: return staged ? k_eval_multi<F, 0, 8, RED, staged_class<F>(8, RED)> : k_eval_multi<F, 0, 8, RED>;
             case 1: return k_eval_multi<F, 9, 12, RED>;
             case 2: return k_eval_multi<F, 13, 16, RED>;
             case 3: return k_eval_multi<F, 17, 20, RED>;
@@ -369,6 +506,7 @@ struct MultiShape {
     KClass cls[kMaxClasses];
     int S[kMaxClasses];
     int64_t per_unit[kMaxClasses];
+    bool staged[kMaxClasses];
 };
 
 MultiShape multi_shape(const thoi_eval_opts* o)
@@ -378,7 +516,8 @@ MultiShape multi_shape(const thoi_eval_opts* o)
     const KClass* c = f64 ? classes_for<double>(sh.ncls) : classes_for<float>(sh.ncls);
     for (int i = 0; i < sh.ncls; ++i) {
         sh.cls[i] = c[i];
-        sh.S[i] = f64 ? multi_per_lane<double>(c[i].hi) : multi_per_lane<float>(c[i].hi);
+        sh.staged[i] = !f64 && o->out_dtype == THOI_DTYPE_F32 && staged_class<float>(c[i].hi, o->reduce != nullptr);
+        sh.S[i] = sh.staged[i] ? kStageS : (f64 ? multi_per_lane<double>(c[i].hi) : multi_per_lane<float>(c[i].hi));
         sh.per_unit[i] = (int64_t)kTile * sh.S[i] * default_seg_tiles(o);
     }
     return sh;
@@ -582,10 +721,12 @@ thoi_status launch_multi(const double* Sigma, const int32_t* N_d, const int32_t*
         for (int c = 0; c < sh.ncls; ++c) {
             if (units[c] == 0) continue;
             const int64_t G = class_grid(units[c], opts->grid_blocks);
-            const size_t lds = lane_stage_bytes(nmax, sh.cls[c].hi, opts->precision == THOI_FP64 ? 8 : 4) + red_lds(red);
+            const bool staged = sh.staged[c];
+            const size_t lds = lane_stage_bytes(nmax, sh.cls[c].hi + (staged ? 1 : 0), opts->precision == THOI_FP64 ? 8 : 4) +
+                               red_lds(red) + (staged ? kTile / 64 * stage_bytes(a.write_H) : 0);
             MultiKernel kern;
-            if (opts->precision == THOI_FP64) kern = reduce ? multi_kernel_r<double, true>(c) : multi_kernel_r<double, false>(c);
-            else kern = reduce ? multi_kernel_r<float, true>(c) : multi_kernel_r<float, false>(c);
+            if (opts->precision == THOI_FP64) kern = reduce ? multi_kernel_r<double, true>(c, staged) : multi_kernel_r<double, false>(c, staged);
+            else kern = reduce ? multi_kernel_r<float, true>(c, staged) : multi_kernel_r<float, false>(c, staged);
             hipLaunchKernelGGL(kern, dim3((unsigned)G), dim3(kTile), lds, fan.stream(b++), a, m, c, units[c], nmax, red);
         }
     }
