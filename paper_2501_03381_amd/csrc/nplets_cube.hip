@@ -6,8 +6,7 @@
 //   log a_j = log (R_S^-1)_jj = ld(S \ j) - ld(S)
 // (the cofactor identity), and an n-plet costs one pivot and k table reads instead of a factorisation
 // and an inversion of order k ("The combinatorial explosion": the number of subsets stays, the k^3
-// per subset goes).  A reduction needs the value itself of few n-plets, so the table (FP64 for either
-// precision) only filters: an n-plet whose bin is certain and which cannot enter a list is counted, the
+// per subset goes).  A reduction needs the value itself of few n-plets, so the table only filters: an n-plet whose bin is certain and which cannot enter a list is counted, the
 // rest is evaluated as the lane and pair engines do (nplets_cube_verify.hip), and the results are theirs
 // bit for bit.
 //
@@ -21,10 +20,15 @@
 //  - k_cube_filter, one wavefront per (row, size): the n-plets P + (subsets of one size) have
 //    consecutive global indices and read consecutive entries of the rows of P without one member;
 //    removing one of the ten variables stays inside the row (a table of neighbours in LDS).
-// Bound by VALU issue (57% busy) and the latency of the table reads (k + 1 of 8 bytes per n-plet).  A
-// factorisation per n-plet against the table, top-100 and 256 bins, orders 3..N:
-//   N = 30  FP32 + refinement 66.2 / 31.7 ms (build 8, filter 23, open n-plets 2)   FP64 424 / 34.6 ms
-//   N = 27  FP32 + refinement 7.74 / 4.24 ms      N = 25  FP64 4.75 / 1.62 ms      N = 22  FP64 1.66 / 0.48 ms
+// Bound by VALU issue (the build: logarithms and eliminations in FP64; the filter, 57% busy) and the
+// latency of the table reads (k + 1 per n-plet).  A factorisation per n-plet against the table, top-100 and
+// 256 bins, orders 3..N:
+//   N = 30  FP32 + refinement 66.2 / 30.1 ms (build 6.2, filter 22, the rest of the last evaluation)
+//           FP64 424 / 34.2 ms        N = 27  FP32 + refinement 7.74 / 4.12 ms
+//   N = 25  FP64 4.75 / 1.25 ms (build 0.20, bounds 0.09, filter 0.61, open n-plets 0.20, final merge 0.06)
+//   N = 22  FP64 1.66 / 0.51 ms
+// Without bounds of the small orders (their lists open on every n-plet) N = 25 took 1.60 ms, and with an
+// exponential per table read no more and no less.
 // Taking the table's values themselves (no second evaluation) measured 1.05 ms at N = 25, with errors
 // against 64-bit references of 1e-14 instead of 2e-15.
 #include "nplets_cube.hpp"
@@ -96,18 +100,42 @@ __device__ __forceinline__ void cube_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 1/x to the last bit or so (two Newton steps on the hardware estimate); the caller tests x.
+// Entries of the table.  FP64: the value.  FP32: the filter's margin is a thousand times an FP32 rounding,
+// so the value in fixed point, 2^-25 each (half the bytes, exact sums); kFixBad: not positive definite
+// or below -64.
+constexpr double kFixScale = 33554432.0;                // 2^25
+constexpr int32_t kFixBad = 0x7fffffff;
+template <bool F32>
+struct TableOf { typedef double T; };
+template <>
+struct TableOf<true> { typedef int32_t T; };
+template <bool F32>
+using Tab = typename TableOf<F32>::T;
+
+__device__ __forceinline__ void encode(double ld, double& e) { e = ld; }
+__device__ __forceinline__ void encode(double ld, int32_t& e)
+{
+    e = ld > -63.5 && ld < 63.5 ? __double2int_rn(ld * kFixScale) : kFixBad;
+}
+__device__ __forceinline__ double decode(double e) { return e; }
+__device__ __forceinline__ double decode(int32_t e) { return e == kFixBad ? __builtin_nan("") : (double)e * (1.0 / kFixScale); }
+
+// 1/x, two Newton steps on the hardware estimate for the last bit or so, one (about 1e-14) for the fixed
+// point table; the caller tests x.
+template <bool F32>
 __device__ __forceinline__ double fast_rcp(double x)
 {
     double y = __builtin_amdgcn_rcp(x);
     y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    if constexpr (!F32) y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return y;
 }
 
 // log x for a pivot x (in (0, 1] up to rounding); NaN for x <= 0.  x = m 2^e with m in [sqrt(1/2),
 // sqrt(2)), log m = 2 atanh(s) with s = (m - 1) / (m + 1), |s| < 0.1716: the series to s^21 leaves less
-// than 1e-18 relative, and m - 1 is exact, so pivots close to 1 keep their relative accuracy.  21 of
-// the library's logarithms were a third of the row's instructions.
+// than 1e-18 relative (to s^11, 2e-11, for the fixed point table), and m - 1 is exact, so pivots close to 1
+// keep their relative accuracy.  21 of the library's logarithms were a third of the row's instructions.
+template <bool F32>
 __device__ __forceinline__ double pivot_log(double x)
 {
     double m = __builtin_amdgcn_frexp_mant(x);
@@ -115,16 +143,19 @@ __device__ __forceinline__ double pivot_log(double x)
     const bool low = m < 0.70710678118654752440;
     m = low ? m + m : m;
     e -= low ? 1 : 0;
-    const double f = m - 1.0, den = m + 1.0, r = fast_rcp(den);
+    const double f = m - 1.0, den = m + 1.0, r = fast_rcp<F32>(den);
     double s = f * r;
-    s = __builtin_fma(__builtin_fma(-den, s, f), r, s);   // the quotient's last bit
+    if constexpr (!F32) s = __builtin_fma(__builtin_fma(-den, s, f), r, s);   // the quotient's last bit
     const double z = s * s;
-    double p = 1.0 / 21;
-    p = __builtin_fma(p, z, 1.0 / 19);
-    p = __builtin_fma(p, z, 1.0 / 17);
-    p = __builtin_fma(p, z, 1.0 / 15);
-    p = __builtin_fma(p, z, 1.0 / 13);
-    p = __builtin_fma(p, z, 1.0 / 11);
+    double p = 1.0 / 11;
+    if constexpr (!F32) {
+        p = 1.0 / 21;
+        p = __builtin_fma(p, z, 1.0 / 19);
+        p = __builtin_fma(p, z, 1.0 / 17);
+        p = __builtin_fma(p, z, 1.0 / 15);
+        p = __builtin_fma(p, z, 1.0 / 13);
+        p = __builtin_fma(p, z, 1.0 / 11);
+    }
     p = __builtin_fma(p, z, 1.0 / 9);
     p = __builtin_fma(p, z, 1.0 / 7);
     p = __builtin_fma(p, z, 1.0 / 5);
@@ -138,7 +169,7 @@ __device__ __forceinline__ double pivot_log(double x)
 // Subsets of suffix variables V..9 over the Schur complement s (lower triangle of variables V..9,
 // row i - V): ld of every one into row[position], starting from ld and the subset m of the variables
 // below V.
-template <int V>
+template <bool F32, int V>
 __device__ __forceinline__ void cube_walk(const double (&s)[(kCubeSuffix - V) * (kCubeSuffix - V + 1) / 2 + 1], double ld,
                                           int m, double* __restrict__ row, const uint16_t* __restrict__ spos)
 {
@@ -150,21 +181,22 @@ __device__ __forceinline__ void cube_walk(const double (&s)[(kCubeSuffix - V) * 
         sfor<1, n>([&](auto I) {
             sfor<1, I + 1>([&](auto J) { x[tri(I - 1, J - 1)] = s[tri(I, J)]; });
         });
-        cube_walk<V + 1>(x, ld, m, row, spos);
-        const double p = s[0], inv = fast_rcp(p);
+        cube_walk<F32, V + 1>(x, ld, m, row, spos);
+        const double p = s[0], inv = fast_rcp<F32>(p);
         sfor<1, n>([&](auto I) {
             const double t = s[tri(I, 0)] * inv;
             sfor<1, I + 1>([&](auto J) { y[tri(I - 1, J - 1)] = __builtin_fma(-t, s[tri(J, 0)], s[tri(I, J)]); });
         });
-        cube_walk<V + 1>(y, ld + pivot_log(p), m | (1 << V), row, spos);
+        cube_walk<F32, V + 1>(y, ld + pivot_log<F32>(p), m | (1 << V), row, spos);
     }
 }
 
 // grid (ceil(2^h / 16), datasets of the group), block kBuildThreads: rows P of the table of dataset
 // d0 + blockIdx.y, kBuildRows per wavefront.  Bit h - 1 - v of P is variable v.  Rows with more than kmax
 // members are not needed.
+template <bool F32>
 __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __restrict__ Sigma, int N, int64_t d0,
-                                                              int kmax, double* __restrict__ table)
+                                                              int kmax, Tab<F32>* __restrict__ table)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     double* sR = reinterpret_cast<double*>(smem);                      // [N][N]
@@ -223,7 +255,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
                 cube_wave_sync();
                 const double pj = cl[kCubeSuffix + j];
                 piv = q == j ? pj : piv;
-                const double t = r[kCubeSuffix + j] * fast_rcp(pj);
+                const double t = r[kCubeSuffix + j] * fast_rcp<F32>(pj);
                 sfor<j + 1, kCubePrefix>([&](auto Q) {
                     constexpr int c = Q;
                     if (c < p) r[kCubeSuffix + c] = __builtin_fma(-t, cl[kCubeSuffix + c], r[kCubeSuffix + c]);
@@ -231,7 +263,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
                 sfor<0, kCubeSuffix>([&](auto M) { r[M] = __builtin_fma(-t, cl[M], r[M]); });
             }
         });
-        const double lp = pivot_log(piv);
+        const double lp = pivot_log<F32>(piv);
         double ld = 0.0;
         for (int e = 0; e < p; ++e) ld += __shfl(lp, kCubeSuffix + e, 64);
         // the Schur complement of the ten variables in every lane
@@ -247,8 +279,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
         sfor<0, 6>([&](auto T) {
             constexpr int t = T;
             if ((lane >> t) & 1) {
-                const double pt = s[tri(t, t)], inv = fast_rcp(pt);
-                ld += pivot_log(pt);
+                const double pt = s[tri(t, t)], inv = fast_rcp<F32>(pt);
+                ld += pivot_log<F32>(pt);
                 sfor<t + 1, kCubeSuffix>([&](auto I) {
                     constexpr int i = I;
                     const double f = s[tri(i, t)] * inv;
@@ -263,12 +295,12 @@ __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __re
         sfor<0, 4>([&](auto I) {
             sfor<0, I + 1>([&](auto J) { s4[tri(I, J)] = s[tri(I + 6, J + 6)]; });
         });
-        cube_walk<6>(s4, ld, lane, srow, spos);
+        cube_walk<F32, 6>(s4, ld, lane, srow, spos);
         cube_wave_sync();
         // sizes up to kmax - p are needed, a prefix of the row
         const int need = kmax - p >= kCubeSuffix ? kCubeRow : kSuffix.off[kmax - p + 1];
-        double* out = table + ((int64_t)blockIdx.y << N) + ((int64_t)P << kCubeSuffix);
-        for (int i = lane; i < need; i += 64) out[i] = srow[i];
+        Tab<F32>* out = table + ((int64_t)blockIdx.y << N) + ((int64_t)P << kCubeSuffix);
+        for (int i = lane; i < need; i += 64) encode(srow[i], out[i]);
         cube_wave_sync();                                              // srow and the buffers are reused
     }
 }
@@ -279,94 +311,157 @@ size_t build_lds_bytes(int N)
 }
 
 constexpr int kCubeWide = 2;                           // entries per lane of the reduction
+constexpr int kCubeRun = 256;                          // at least C(10, 5)
 
-// W consecutive entries of a row; 8-byte aligned.
-template <int W>
+// W consecutive entries of a row, aligned as one entry.
+template <int W, typename V>
 struct Entries {
-    double v[W];
+    V v[W];
 };
-template <int W>
-__device__ __forceinline__ Entries<W> load_entries(const double* __restrict__ p)
+template <int W, typename V>
+__device__ __forceinline__ Entries<W, V> load_entries(const V* __restrict__ p)
 {
-    typedef double Pack __attribute__((ext_vector_type(W), aligned(8)));
+    typedef V Pack __attribute__((ext_vector_type(W), aligned(sizeof(V))));
     const Pack x = *reinterpret_cast<const Pack*>(p);
-    Entries<W> r;
+    Entries<W, V> r;
 #pragma unroll
     for (int w = 0; w < W; ++w) r.v[w] = x[w];
     return r;
 }
 
-// sa[w] = sum_j (ld(S \ j) - ld(S)) of entries e .. e + W - 1 of row P (all of size b; len entries of
-// that size, the lane's first at index i among them), j ascending: the members of P (uniform in the
-// wavefront), eight reads in flight, then the b members among the ten, whose positions in the row are
-// nb[i], nb[len + i], ... (entries past the run repeat its last: their sums are not used).  Also mx[w] =
-// max_j of the differences (log of the largest VIF) and ex[w] = sum_j of their exponentials (the sum of
-// the VIFs).
-template <int W>
-__device__ __forceinline__ void cube_leave_one_out(const double* __restrict__ T, uint32_t P, int b, int len, int e, int i,
-                                                   const Entries<W>& t0, const uint16_t* nb, double (&sa)[W],
-                                                   float (&mx)[W], float (&ex)[W])
-{
-    constexpr float kLog2e = 1.442695041f;
+// sum_j (ld(S \ j) - ld(S)) of entries e .. e + W - 1 of row P (all of size b; len entries of
+// that size, the lane's first at index i among them): the members of P (uniform in the wavefront), eight
+// reads in flight, then the b members among the ten, whose positions in the row are nb[i], nb[len + i], ...
+// (entries past the run repeat its last: their sums are not used).  Also mx[w] = max_j of the differences
+// (log of the largest VIF, too large by at most 2^-20 |ld(S)|) and ex[w], a bound of the sum of their
+// exponentials (the sum of the VIFs): the largest of each eight or five, as often as there are terms.
+template <typename V>
+struct OneOut;
+template <>
+struct OneOut<double> {
+    double s = 0.0;
+    // the group's largest value from the high words alone: values are <= 0 (a rounding above 0 counts as
+    // the largest), and of those the largest has the smallest word
+    uint32_t g;
+    __device__ __forceinline__ void open() { g = 0xffffffffu; }
+    __device__ __forceinline__ void add(double v)
+    {
+        s += v;
+        const uint32_t hi = (uint32_t)__double2hiint(v);
+        g = hi < g ? hi : g;
+    }
+    __device__ __forceinline__ float most(double t0) const { return (float)(__hiloint2double((int)g, 0) - t0); }
+    __device__ __forceinline__ double sum(double t0, int k) const { return __builtin_fma(-(double)k, t0, s); }
+};
+template <>
+struct OneOut<int32_t> {
+    int64_t s = 0;
+    int32_t g;
+    __device__ __forceinline__ void open() { g = -kFixBad - 1; }
+    __device__ __forceinline__ void add(int32_t v)
+    {
+        s += v;
+        g = v > g ? v : g;
+    }
+    // (infinite where a member is bad: ex is then, too)
+    __device__ __forceinline__ float most(int32_t t0) const
+    {
+        return g == kFixBad ? __builtin_inff() : (float)((int64_t)g - t0) * (float)(1.0 / kFixScale);
+    }
+    __device__ __forceinline__ double sum(int32_t t0, int k) const
+    {
+        return t0 == kFixBad ? __builtin_nan("") : (double)(s - (int64_t)k * t0) * (1.0 / kFixScale);
+    }
+};
+template <int W, typename V>
+struct LeaveOneOut {
+    OneOut<V> o[W];
+    float mx[W], ex[W];
+    __device__ __forceinline__ LeaveOneOut()
+    {
 #pragma unroll
-    for (int w = 0; w < W; ++w) { sa[w] = 0.0; mx[w] = 0.0f; ex[w] = 0.0f; }
-    auto add = [&](int w, double diff) {
-        sa[w] += diff;
-        const float x = (float)diff;
-        mx[w] = x > mx[w] ? x : mx[w];
-        ex[w] += __builtin_amdgcn_exp2f(x * kLog2e);
-    };
-    uint32_t m = P;
-    while (m) {
-        Entries<W> v[8];
-        uint32_t mm = m;
+        for (int w = 0; w < W; ++w) { mx[w] = 0.0f; ex[w] = 0.0f; }
+    }
+    __device__ __forceinline__ void open()
+    {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            v[u] = t0;
-            if (mm) {
-                const uint32_t bit = 0x80000000u >> __builtin_clz(mm);
-                v[u] = load_entries<W>(T + ((int64_t)(P ^ bit) << kCubeSuffix) + e);
-                mm ^= bit;
-            }
+        for (int w = 0; w < W; ++w) o[w].open();
+    }
+    __device__ __forceinline__ void close(const Entries<W, V>& t0, int n)
+    {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float x = o[w].most(t0.v[w]);
+            mx[w] = x > mx[w] ? x : mx[w];
+            ex[w] = fmaf((float)n, __builtin_amdgcn_exp2f(x * 1.442695041f), ex[w]);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (m) {
-#pragma unroll
-                for (int w = 0; w < W; ++w) add(w, v[u].v[w] - t0.v[w]);
-                m ^= 0x80000000u >> __builtin_clz(m);
-            }
     }
-    const double* row = T + ((int64_t)P << kCubeSuffix);
-    int at_i[W];
+    // the members of P
+    __device__ __forceinline__ void prefix(const V* __restrict__ T, uint32_t P, int e, const Entries<W, V>& t0)
+    {
+        uint32_t m = P;
+        while (m) {
+            Entries<W, V> v[8];
+            uint32_t mm = m;
 #pragma unroll
-    for (int w = 0; w < W; ++w) at_i[w] = i + w < len ? i + w : len - 1;
-    for (int t = 0; t < b; t += 5) {
-        int at[5][W];
-        double v[5][W];
-#pragma unroll
-        for (int u = 0; u < 5; ++u)
-#pragma unroll
-            for (int w = 0; w < W; ++w) at[u][w] = nb[(t + u < b ? t + u : b - 1) * len + at_i[w]];
-#pragma unroll
-        for (int u = 0; u < 5; ++u)
-#pragma unroll
-            for (int w = 0; w < W; ++w) v[u][w] = row[at[u][w]];
-#pragma unroll
-        for (int u = 0; u < 5; ++u)
-            if (t + u < b) {                                           // uniform
-#pragma unroll
-                for (int w = 0; w < W; ++w) add(w, v[u][w] - t0.v[w]);
+            for (int u = 0; u < 8; ++u) {
+                v[u] = t0;
+                if (mm) {
+                    const uint32_t bit = 0x80000000u >> __builtin_clz(mm);
+                    v[u] = load_entries<W, V>(T + ((int64_t)(P ^ bit) << kCubeSuffix) + e);
+                    mm ^= bit;
+                }
             }
+            const int n = __popc(m) - __popc(mm);
+            open();
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (m) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) o[w].add(v[u].v[w]);
+                    m ^= 0x80000000u >> __builtin_clz(m);
+                }
+            close(t0, n);
+        }
     }
-}
+    // the b members among the ten, at row[position - shift]
+    __device__ __forceinline__ void suffix(const V* row, int shift, int b, int len, int i, const Entries<W, V>& t0,
+                                           const uint16_t* nb)
+    {
+        int at_i[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) at_i[w] = i + w < len ? i + w : len - 1;
+        for (int t = 0; t < b; t += 5) {
+            int at[5][W];
+            V v[5][W];
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+#pragma unroll
+                for (int w = 0; w < W; ++w) at[u][w] = nb[(t + u < b ? t + u : b - 1) * len + at_i[w]];
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+#pragma unroll
+                for (int w = 0; w < W; ++w) v[u][w] = row[at[u][w] - shift];
+            open();
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+                if (t + u < b) {                                       // uniform
+#pragma unroll
+                    for (int w = 0; w < W; ++w) o[w].add(v[u][w]);
+                }
+            close(t0, b - t < 5 ? b - t : 5);
+        }
+    }
+};
 
 // How far Omega and the VIFs of a factorisation per n-plet (FP32 or FP64) may be from the table's.  With
 // E the perturbation of R_S by rounding it and factoring it (entries of a few units u = 2^-24 or 2^-53),
 // log det moves by tr(R_S^-1 E) and log a_j by (R_S^-1 E R_S^-1)_jj / a_j, to first order; |R_S^-1|_ij
 // <= sqrt(a_i a_j), so both are at most |E| (sum sqrt a)^2 <= |E| k sum a.  Taken: 4 u k sum_j a_j in FP32
 // (about 200 times what the engines differ by on the test systems) and 64 u k sum_j a_j in FP64, where a
-// wide margin costs nothing, plus the rounding of the measures.
+// wide margin costs nothing, plus the rounding of the measures and of the table's sum (k terms of up to
+// |ld| = 2 |TC|, each addition to within u of a sum of up to k |ld|; fixed point: half a unit in each of up
+// to 25 entries).
 struct Margin {
     double rel;              // of log det, log a_j, and relative of a_j
     double round;
@@ -377,19 +472,19 @@ struct Margin {
     }
 };
 template <bool F32>
-__device__ __forceinline__ Margin margin_of(int k, float mx, float ex, float tau)
+__device__ __forceinline__ Margin margin_of(int k, double ld, float mx, float ex, float tau)
 {
     Margin m;
     if constexpr (F32) {
         const float rel = 4.0f * 5.9604645e-8f * (float)k * ex;
-        const float v = __builtin_amdgcn_exp2f(mx * 1.442695041f), d = rel + 1e-5f;
-        m.rel = (double)rel;
+        const float v = __builtin_amdgcn_exp2f(mx * 1.442695041f), d = rel + 1e-5f + 2e-6f * fabsf((float)ld);
+        m.rel = (double)rel + 4e-7;
         m.round = 2.4e-7;
         m.vif = !(v * (1.0f + d) < tau) ? (v > tau * (1.0f + d) ? 2 : 1) : 0;
         if (!(rel < 0.25f)) m.vif = m.vif == 0 ? 1 : m.vif;
     } else {
         m.rel = 64.0 * 1.1102230246251565e-16 * k * (double)ex;
-        m.round = 4e-15;
+        m.round = 4e-15 + 4.5e-16 * (double)(k * k);
         m.vif = 0;
     }
     return m;
@@ -402,21 +497,20 @@ __device__ __forceinline__ Margin margin_of(int k, float mx, float ex, float tau
 // share of the K best reach; all groups together then hold K distinct n-plets up to the largest of
 // these keys, and the reduction meets them again.  A wavefront takes the 64-entry piece of a run that
 // holds an evenly spaced rank, so its reads are as coalesced as the reduction's (n-plets at single
-// ranks, scattered over the table: 224 us against 85 at N = 25).  Orders with
-// fewer n-plets than kSampleMin have no bound: below 64 ranks apart two pieces could coincide.
+// ranks, scattered over the table: 224 us against 85 at N = 25).  Small orders
+// take fewer pieces: less than 64 ranks apart two could coincide.
 // ------------------------------------------------------------------------------------------------
 constexpr int kSampleThreads = 1024;
 constexpr int kSamplePer = 8;                          // pieces per wavefront
 constexpr int kSampleGroups = 8;
 constexpr uint32_t kSamplePieces = kSampleThreads / 64 * kSamplePer * kSampleGroups;
-constexpr uint32_t kSampleMin = kSamplePieces * 64;
 
 // grid (kSampleGroups, orders, datasets of the group): sbound[dataset of the group][order][group][2].
 // The values are taken at the unfavourable end of what the factorisation may make of them; FP32:
 // n-plets near or above the refinement threshold are left out.
 template <bool F32>
 __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, CubeTable tab, int K, int64_t d0,
-                                                                const double* __restrict__ table,
+                                                                const Tab<F32>* __restrict__ table,
                                                                 uint64_t* __restrict__ sbound)
 {
     __shared__ uint32_t sbin[kCubeMaxN * (kCubeMaxN + 1)];
@@ -430,21 +524,23 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint64_t* out = sbound + (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * kSampleGroups + blockIdx.x) * 2;
     const uint32_t total = (uint32_t)kPascal.v[N][k];
-    if (total < kSampleMin) {                          // uniform
-        if (tid < 2) out[tid] = kKeyEmpty;
-        return;
-    }
+    const uint32_t pieces = total / 64 < kSamplePieces ? total / 64 : kSamplePieces;
     for (int i = tid; i < N * (k + 1); i += kSampleThreads) sbin[i] = (uint32_t)kPascal.v[i / (k + 1)][i % (k + 1)];
     for (int i = tid; i < kCubeSuffix * kCubeRow / 2; i += kSampleThreads) snbr[i] = kSuffix.nbr[i];
     if (tid == 0) bias_for(a.bias, k, sbias[0], sbias[1], sbias[2]);
     __syncthreads();
-    const double* T = table + ((int64_t)blockIdx.z << N);
+    const Tab<F32>* T = table + ((int64_t)blockIdx.z << N);
     double om[kSamplePer], mu[kSamplePer];
     int nv = 0;
 #pragma unroll
     for (int u = 0; u < kSamplePer; ++u) {
         const uint32_t s = ((uint32_t)u * (kSampleThreads / 64) + wv) * kSampleGroups + blockIdx.x;
-        uint32_t r = (uint32_t)((uint64_t)s * total / kSamplePieces);
+        if (s >= pieces) {                             // uniform in the wavefront
+            om[u] = __builtin_nan("");
+            mu[u] = 0.0;
+            continue;
+        }
+        uint32_t r = (uint32_t)((uint64_t)s * total / pieces);
         // the r-th k-subset in lexicographic order, as prefix bits and suffix bits (uniform)
         uint32_t P = 0, B = 0;
         int m = k - 1;
@@ -465,14 +561,14 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
         const int i = (kSuffix.pos[B] - o0) / 64 * 64 + lane;
         const bool on = i < len;
         const int e = o0 + (on ? i : 0);
-        const Entries<1> ld = load_entries<1>(T + ((int64_t)P << kCubeSuffix) + e);
-        double sum[1];
-        float mx[1], ex[1];
-        cube_leave_one_out<1>(T, P, b, len, e, on ? i : 0, ld, snbr + kSuffix.noff[b], sum, mx, ex);
-        const double t0 = ld.v[0], sa = sum[0];
+        const Entries<1, Tab<F32>> ld = load_entries<1, Tab<F32>>(T + ((int64_t)P << kCubeSuffix) + e);
+        LeaveOneOut<1, Tab<F32>> lv;
+        lv.prefix(T, P, e, ld);
+        lv.suffix(T + ((int64_t)P << kCubeSuffix), 0, b, len, on ? i : 0, ld, snbr + kSuffix.noff[b]);
+        const double t0 = decode(ld.v[0]), sa = lv.o[0].sum(ld.v[0], k);
         const double TC = -0.5 * t0 + sbias[0], DTC = 0.5 * (t0 + sa) + sbias[1];
         om[u] = on && isfinite(t0) && isfinite(sa) ? TC - DTC : __builtin_nan("");
-        const Margin mg = margin_of<F32>(k, mx[0], ex[0], a.vif_tau);
+        const Margin mg = margin_of<F32>(k, t0, lv.mx[0], lv.ex[0], a.vif_tau);
         mu[u] = mg.value(TC, DTC);
         if (mg.vif != 0 || !isfinite(mu[u])) om[u] = __builtin_nan("");
     }
@@ -538,11 +634,12 @@ __device__ __forceinline__ void flush_open(const CubeOpen& o, int k, const uint3
 // left open and evaluated by k_cube_verify.
 template <bool F32>
 __global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, RedArgs red, CubeOpen opn, int64_t d0,
-                                                     const double* __restrict__ table)
+                                                     const Tab<F32>* __restrict__ table)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t sopen[4 * kOpenBuf];
     __shared__ uint16_t smask[kCubeRow];
+    __shared__ int32_t srun[F32 ? 4 * kCubeRun : 1];
     __shared__ double sbias[3];
     const int N = a.N, h = N - kCubeSuffix;
     // all orders of one chunk of rows run together on one XCD (workgroups are dealt to the 8 XCDs
@@ -574,8 +671,9 @@ __global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, 
     }
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint32_t* sbuf = sopen + wv * kOpenBuf;
+    int32_t* run = srun + (F32 ? wv * kCubeRun : 0);
     int nbuf = 0;                                                      // uniform in the wavefront
-    const double* T = table;
+    const Tab<F32>* T = table;
     const uint32_t nrows = 1u << h;
     const uint32_t r0 = (uint32_t)tab.row0 + (uint32_t)chunk * (uint32_t)tab.per;
     const uint32_t r1 = min(r0 + (uint32_t)tab.per, nrows);
@@ -595,24 +693,47 @@ __global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, 
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
         const uint32_t rank0 = (uint32_t)kPascal.v[N][k] - 1u - term;
+        // FP32: the row's subsets of one variable less, where those without one of the ten are, go into LDS
+        // once the members of P are under way (N = 30: 31.5 ms without, 30.1 with; in FP64 the registers
+        // cost a wavefront per SIMD, N = 27: 4.11 without, 4.20 with)
+        const int om = b > 0 ? kSuffix.off[b - 1] : 0, lenm = b > 0 ? o0 - om : 0;
+        int32_t less[kCubeRun / 64];
+        if constexpr (F32) {
+#pragma unroll
+            for (int u = 0; u < kCubeRun / 64; ++u) {
+                less[u] = 0;
+                if (64 * u + lane < lenm) less[u] = T[((int64_t)P << kCubeSuffix) + om + 64 * u + lane];
+            }
+        }
         for (int i0 = 0; i0 < len; i0 += 64 * kCubeWide) {
             const int i = i0 + lane * kCubeWide;
             const bool on = i < len;
             const int e = o0 + (on ? i : 0);
-            const Entries<kCubeWide> ld = load_entries<kCubeWide>(T + ((int64_t)P << kCubeSuffix) + e);
-            double sa[kCubeWide];
-            float mx[kCubeWide], ex[kCubeWide];
-            cube_leave_one_out<kCubeWide>(T, P, b, len, e, on ? i : 0, ld, snbr + kSuffix.noff[b], sa, mx, ex);
+            const Entries<kCubeWide, Tab<F32>> ld = load_entries<kCubeWide, Tab<F32>>(T + ((int64_t)P << kCubeSuffix) + e);
+            LeaveOneOut<kCubeWide, Tab<F32>> lv;
+            lv.prefix(T, P, e, ld);
+            if constexpr (F32) {
+                if (i0 == 0) {
+#pragma unroll
+                    for (int u = 0; u < kCubeRun / 64; ++u) run[64 * u + lane] = less[u];
+                    cube_wave_sync();
+                }
+                lv.suffix(run, om, b, len, on ? i : 0, ld, snbr + kSuffix.noff[b]);
+            } else {
+                lv.suffix(T + ((int64_t)P << kCubeSuffix), 0, b, len, on ? i : 0, ld, snbr + kSuffix.noff[b]);
+            }
 #pragma unroll
             for (int w = 0; w < kCubeWide; ++w) {
                 const bool in = i + w < len;
                 const int64_t pos = pc.pos0 + rank0 + i + w;
-                const double TC = -0.5 * ld.v[w] + sbias[0], DTC = 0.5 * (ld.v[w] + sa[w]) + sbias[1];
+                const double t0 = decode(ld.v[w]);
+                const double TC = -0.5 * t0 + sbias[0], sa = lv.o[w].sum(ld.v[w], k);
+                const double DTC = 0.5 * (t0 + sa) + sbias[1];
                 const double v = TC - DTC;
-                const Margin mg = margin_of<F32>(k, mx[w], ex[w], a.vif_tau);
-                const bool bad = !isfinite(ld.v[w]) || !isfinite(sa[w]) || !(ex[w] < 3e38f);
-                const bool refine = F32 && in && (bad || mg.vif == 2);
-                // open: the VIF near the threshold, Omega near a bin edge or near the lists
+                const Margin mg = margin_of<F32>(k, t0, lv.mx[w], lv.ex[w], a.vif_tau);
+                const bool bad = !isfinite(t0) || !isfinite(sa) || !(lv.ex[w] < 3e38f);
+                const bool refine = F32 && in && !bad && mg.vif == 2;
+                // open: no value in the table, the VIF near the threshold, Omega near a bin edge or near the lists
                 bool open = in && !refine && (bad || mg.vif == 1);
                 const double mu = mg.value(TC, DTC);
                 if (red.topk > 0) open = open || (in && !refine && (v + mu >= top || v - mu <= bottom));
@@ -653,6 +774,7 @@ __global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, 
                 nbuf = 0;
             }
         }
+        if constexpr (F32) cube_wave_sync();                           // the next run overwrites the buffer
     }
     flush_open(opn, k, sbuf, nbuf, lane);
     red_end(S, hist, a.hdr, (int)d, k);
@@ -695,16 +817,19 @@ CubeTable cube_table(int N, int kmin, int kmax, int64_t rows)
 int64_t cube_blocks(const CubeTable& t) { return (int64_t)(t.chunks + 7) / 8 * 8 * t.n; }
 
 // Datasets whose tables are held at a time: up to 256 MB together, at least one dataset's.
-int64_t cube_group(int32_t N, int64_t D)
+int64_t cube_group(int32_t N, int64_t D, bool f32)
 {
-    const int64_t g = (int64_t(1) << 28) >> (N + 3);
+    const int64_t g = (int64_t(1) << 28) >> (N + (f32 ? 2 : 3));
     return g < 1 ? 1 : (g < D ? g : D);
 }
 
-// Rows filtered between two evaluations of the open lists, and the largest number of n-plets of order k
-// in such an aligned block of rows: the high prefix bits fix c members, the rest is free.
+// Rows filtered in one launch.  A block of rows is evaluated while the next one is filtered, and its lists
+// tighten the bounds of those after that; the fork and join cost about 45 us a block (N = 25: one block
+// 1.26 ms, two 1.32, four 1.50; N = 30, FP32: four blocks 31.4 ms, eight 31.9).
 constexpr int kFilterBits = 18;
 int filter_bits(int N) { return N - kCubeSuffix < kFilterBits ? N - kCubeSuffix : kFilterBits; }
+// The largest number of n-plets of order k in such an aligned block of rows: the high prefix bits fix c
+// members, the rest is free.
 int64_t open_cap(int N, int k)
 {
     const int free_vars = filter_bits(N) + kCubeSuffix;
@@ -717,25 +842,28 @@ int64_t open_cap(int N, int k)
 }
 
 struct CubeMem {
-    size_t sample, cnt, list, total;                   // behind the tables
+    size_t sample, cnt, list[2], total;                // behind the tables; a list for every other block
     CubeOpen open;
 };
-CubeMem cube_mem(int N, int64_t D, int kmin, int kmax)
+CubeMem cube_mem(int N, int64_t D, int kmin, int kmax, bool f32)
 {
     CubeMem m{};
-    const int64_t g = cube_group(N, D);
-    size_t off = (size_t)g << (N + 3);
+    const int64_t g = cube_group(N, D, f32);
+    size_t off = (size_t)g << (N + (f32 ? 2 : 3));
     m.sample = off;
     off = align_up(off + (size_t)g * (N + 1) * kSampleGroups * 16, 256);
     m.cnt = off;
-    off += 256;
-    m.list = off;
+    off += 512;
     int64_t o = 0;
     for (int k = kmin; k <= kmax; ++k) {
         m.open.off[k] = o;
         o += open_cap(N, k);
     }
-    off = align_up(off + (size_t)o * 4, 256);
+    const int lists = filter_bits(N) < N - kCubeSuffix || D > 1 ? 2 : 1;
+    for (int i = 0; i < 2; ++i) {
+        m.list[i] = i < lists ? off : m.list[0];
+        if (i < lists) off = align_up(off + (size_t)o * 4, 256);
+    }
     m.total = off;
     return m;
 }
@@ -763,7 +891,7 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
     return kmax >= (f32 ? 12 : 8) && all >= need / (f32 ? 2 : 8);
 }
 
-size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax) { return cube_mem(N, D, kmin, kmax).total; }
+size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32) { return cube_mem(N, D, kmin, kmax, f32).total; }
 
 int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax)
 {
@@ -771,23 +899,27 @@ int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax)
     return (rows >> filter_bits(N)) * (kmax - kmin + 1) * kVerifyBlocks * D;
 }
 
-void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
-                 const std::function<void(hipStream_t)>& beside, hipStream_t s)
+namespace {
+
+template <bool F32>
+void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool serial, void* mem,
+            const std::function<void(hipStream_t)>& beside, hipStream_t s)
 {
     static_assert(sizeof(kSuffixHost.nbr) == kCubeSuffix * kCubeRow, "one neighbour per element");
     const int64_t rows = int64_t(1) << (a.N - kCubeSuffix);
     const int64_t step = int64_t(1) << filter_bits(a.N);
     CubeTable tab = cube_table(a.N, kmin, kmax, step);
     const int64_t blocks = cube_blocks(tab);
-    const int64_t group = cube_group(a.N, a.D);
-    CubeMem m = cube_mem(a.N, a.D, kmin, kmax);
+    const int64_t group = cube_group(a.N, a.D, F32);
+    CubeMem m = cube_mem(a.N, a.D, kmin, kmax, F32);
     char* base = static_cast<char*>(mem);
-    double* table = static_cast<double*>(mem);
+    Tab<F32>* table = static_cast<Tab<F32>*>(mem);
     uint64_t* sbound = reinterpret_cast<uint64_t*>(base + m.sample);
-    m.open.list = reinterpret_cast<uint32_t*>(base + m.list);
-    m.open.cnt = reinterpret_cast<uint32_t*>(base + m.cnt);
-    const auto sample = f32 ? k_cube_sample<true> : k_cube_sample<false>;
-    const auto filter = f32 ? k_cube_filter<true> : k_cube_filter<false>;
+    CubeOpen open[2] = {m.open, m.open};
+    for (int i = 0; i < 2; ++i) {
+        open[i].list = reinterpret_cast<uint32_t*>(base + m.list[i]);
+        open[i].cnt = reinterpret_cast<uint32_t*>(base + m.cnt + 256 * i);
+    }
     for (int64_t d0 = 0; d0 < a.D; d0 += group) {
         const int64_t nd = d0 + group < a.D ? group : a.D - d0;
         {
@@ -795,25 +927,38 @@ void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool
             FanScope fan(s, two && !serial ? 2 : 1);
             if (two) beside(fan.stream(1));
             const int64_t nb = (rows + kBuildWaves * kBuildRows - 1) / (kBuildWaves * kBuildRows);
-            hipLaunchKernelGGL(k_cube_build, dim3((unsigned)nb, (unsigned)nd), dim3(kBuildThreads), build_lds_bytes(a.N),
+            hipLaunchKernelGGL(k_cube_build<F32>, dim3((unsigned)nb, (unsigned)nd), dim3(kBuildThreads), build_lds_bytes(a.N),
                                fan.stream(0), a.Sigma, a.N, d0, kmax, table);
         }
         if (red.topk > 0) {
-            hipLaunchKernelGGL(sample, dim3(kSampleGroups, (unsigned)tab.n, (unsigned)nd), dim3(kSampleThreads), 0, s, a, tab,
+            hipLaunchKernelGGL(k_cube_sample<F32>, dim3(kSampleGroups, (unsigned)tab.n, (unsigned)nd), dim3(kSampleThreads), 0, s, a, tab,
                                red.topk, d0, table, sbound);
             hipLaunchKernelGGL(k_cube_bounds, dim3((unsigned)tab.n, (unsigned)nd), dim3(64), 0, s, tab, red, d0, sbound);
         }
-        // one dataset at a time, block of rows after block of rows
-        for (int64_t e = 0; e < nd; ++e) {
-            for (int64_t r0 = 0; r0 < rows; r0 += step) {
-                tab.row0 = (int32_t)r0;
-                ws_clear(m.open.cnt, 256, s);
-                hipLaunchKernelGGL(filter, dim3((unsigned)blocks), dim3(256), filter_lds_bytes(red), s, a, tab, red, m.open,
-                                   d0 + e, table + (e << a.N));
-                cube_verify_launch(a, tab, m.open, red, d0 + e, f32, serial, s);
+        // one dataset at a time, block of rows after block of rows, each evaluated beside the next filter
+        const int64_t steps = nd * (rows / step);
+        for (int64_t i = 0; i <= steps; ++i) {
+            FanScope fan(s, serial ? 1 : 6);
+            if (i < steps) {
+                const int64_t e = i / (rows / step);
+                tab.row0 = (int32_t)(i % (rows / step) * step);
+                ws_clear(open[i & 1].cnt, 256, fan.stream(0));
+                hipLaunchKernelGGL(k_cube_filter<F32>, dim3((unsigned)blocks), dim3(256), filter_lds_bytes(red), fan.stream(0), a, tab, red,
+                                   open[i & 1], d0 + e, table + (e << a.N));
             }
+            // (the last block has the caller's stream as well)
+            if (i > 0) cube_verify_launch(a, tab, open[(i - 1) & 1], red, d0 + (i - 1) / (rows / step), F32, fan, i < steps ? 1 : 0);
         }
     }
+}
+
+}  // namespace
+
+void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
+                 const std::function<void(hipStream_t)>& beside, hipStream_t s)
+{
+    if (f32) launch<true>(a, red, kmin, kmax, serial, mem, beside, s);
+    else launch<false>(a, red, kmin, kmax, serial, mem, beside, s);
 }
 
 }  // namespace thoi

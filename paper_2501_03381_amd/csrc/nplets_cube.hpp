@@ -38,15 +38,16 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
 // Largest order the cube engine takes (FP32: the lane engine's; orders above go to the pair engine).
 int cube_kmax(bool f32, int kmax);
 // Bytes behind the segments and the queue: tables, sample keys and open lists.
-size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax);
+size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32);
 // Segments the reduction leaves (an upper bound).
 int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax);
 // beside (or empty): launches of the call that do not touch the table, put on a stream beside the first
 // table's build.  serial: everything on s.
 void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
                  const std::function<void(hipStream_t)>& beside, hipStream_t s);
-// The open n-plets of dataset d, evaluated as the lane and pair engines do.
+// The open n-plets of dataset d, evaluated as the lane and pair engines do, on branches `from` to
+// `from` + 4 of the scope (modulo what it has).
 void cube_verify_launch(const EvalArgs& a, const CubeTable& tab, const CubeOpen& open, const RedArgs& red, int64_t d,
-                        bool f32, bool serial, hipStream_t s);
+                        bool f32, const FanScope& fan, int from);
 
 }  // namespace thoi

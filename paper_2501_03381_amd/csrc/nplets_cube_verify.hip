@@ -161,28 +161,27 @@ void launch_class(const EvalArgs& a, const CubeTable& tab, const CubeOpen& open,
 }  // namespace
 
 void cube_verify_launch(const EvalArgs& a, const CubeTable& tab, const CubeOpen& open, const RedArgs& red, int64_t d,
-                        bool f32, bool serial, hipStream_t s)
+                        bool f32, const FanScope& fan, int from)
 {
     // short lists: each class is bound by the latency of its longest lane, so they run side by side
-    FanScope fan(s, serial ? 1 : 5);
     if (f32) {
-        launch_class<float, 17, 20>(a, tab, open, red, d, fan.stream(0));
-        launch_class<float, 21, 24>(a, tab, open, red, d, fan.stream(1));
-        launch_class<float, 13, 16>(a, tab, open, red, d, fan.stream(2));
-        launch_class<float, 9, 12>(a, tab, open, red, d, fan.stream(3));
-        launch_class<float, 3, 8>(a, tab, open, red, d, fan.stream(4));
+        launch_class<float, 17, 20>(a, tab, open, red, d, fan.stream(from));
+        launch_class<float, 21, 24>(a, tab, open, red, d, fan.stream(from + 1));
+        launch_class<float, 13, 16>(a, tab, open, red, d, fan.stream(from + 2));
+        launch_class<float, 9, 12>(a, tab, open, red, d, fan.stream(from + 3));
+        launch_class<float, 3, 8>(a, tab, open, red, d, fan.stream(from + 4));
         return;
     }
-    launch_class<double, 15, 18>(a, tab, open, red, d, fan.stream(0));
-    launch_class<double, 11, 14>(a, tab, open, red, d, fan.stream(1));
-    launch_class<double, 7, 10>(a, tab, open, red, d, fan.stream(2));
-    launch_class<double, 3, 6>(a, tab, open, red, d, fan.stream(3));
+    launch_class<double, 15, 18>(a, tab, open, red, d, fan.stream(from));
+    launch_class<double, 11, 14>(a, tab, open, red, d, fan.stream(from + 1));
+    launch_class<double, 7, 10>(a, tab, open, red, d, fan.stream(from + 2));
+    launch_class<double, 3, 6>(a, tab, open, red, d, fan.stream(from + 3));
     int first = 0;
     const int n = pieces(tab, kF64LaneMax + 1, kCubeMaxN, first);
     if (n > 0) {
         const size_t lds = ((size_t)a.N * a.N * 8 + 16 * (size_t)a.N + (size_t)a.N * (kCubeMaxN + 1) * 4 + 15) / 16 * 16 +
                            red_lds_bytes(red.topk, red.bins);
-        hipLaunchKernelGGL(k_cube_verify_pair, dim3(kVerifyBlocks, (unsigned)n), dim3(kTile), lds, fan.stream(4), a, tab, open,
+        hipLaunchKernelGGL(k_cube_verify_pair, dim3(kVerifyBlocks, (unsigned)n), dim3(kTile), lds, fan.stream(from + 4), a, tab, open,
                            red, d, first);
     }
 }

@@ -443,7 +443,7 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
     if (cube) {
         const bool f32 = opts->precision != THOI_FP64;
         w.table_off = off;
-        off = align_up(off + cube_bytes(N, D, sel->kmin, cube_kmax(f32, sel->kmax)), 256);
+        off = align_up(off + cube_bytes(N, D, sel->kmin, cube_kmax(f32, sel->kmax), f32), 256);
     }
     w.total = off;
     return w;

@@ -116,6 +116,20 @@ def test_filtered_fp32_is_the_lane_engine_bit_for_bit(env, kmin, kmax, K, bins, 
         assert 0 < int((res[0][-1] == B.THOI_NPLET_REFINED).sum()) < n
 
 
+# from 29 variables on the rows go in several blocks, each evaluated beside the next one's filter
+@pytest.mark.parametrize("prec,kmin,kmax", [("fp64", 4, 8), ("fp32_refine", 3, 12)])
+def test_blocks_of_rows(env, prec, kmin, kmax):
+    torch, api, B, synth = env
+    S = torch.from_numpy(np.cov(synth.factor_model(np.random.default_rng(29), 2000, 29, 6).T)).cuda()
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] blocks {prec} orders {kmin}..{kmax} {e}", flush=True)
+        st = api.nplets_reduce(S, orders=(kmin, kmax), topk=50, hist_bins=100, hist_range=(-6, 6), engine=e, precision=prec)
+        res.append((st.top_val, st.top_g, st.hist))
+    for x, y in zip(*res):
+        assert torch.equal(torch.nan_to_num(x.double(), nan=77.0), torch.nan_to_num(y.double(), nan=77.0))
+
+
 def test_exchangeable_variables_tie_by_index(env):
     """Equal sub-matrices give equal values: of a compound-symmetric matrix every n-plet of an order ties, so
     the lists are the first indices of the order."""
