@@ -880,15 +880,25 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
     // orders 1 and 2 have Omega = 0 up to rounding: their lists would be ordered by other rounding
     if (sel->kmin < 3) return false;
     if (opts->engine != THOI_ENGINE_AUTO || N < (f32 ? kCubeMinN32 : kCubeMinN) || N > kCubeMaxN) return false;
-    // whole orders only, and enough of the subsets that the table holds
-    int64_t all = 0, need = 0;
+    // whole orders only
+    int64_t all = 0;
     for (int k = sel->kmin; k <= sel->kmax; ++k) all += (int64_t)binom_u64(N, k);
     if (sel->g_begin != 0 || sel->g_count != all) return false;
-    const int kmax = cube_kmax(f32, sel->kmax);
-    all = 0;
-    for (int k = sel->kmin; k <= kmax; ++k) all += (int64_t)binom_u64(N, k);
-    for (int k = 0; k <= kmax; ++k) need += (int64_t)binom_u64(N, k);
-    return kmax >= (f32 ? 12 : 8) && all >= need / (f32 ? 2 : 8);
+    // Estimated times in ns.  A factorisation per n-plet (prefix sharing and the pair engine in FP64, the
+    // lane engine's classes in FP32): 0.09 up to order 18 and 2.7 above; 0.05 up to order 12, 0.07 above.
+    // The table: 6 per row of up to kmax members, whatever sizes are needed, 0.027 per n-plet, 40,000 for
+    // the additional launches.  Measured, a factorisation per n-plet / the table, ms (orders):
+    //   FP64  21 (3..21) 1.10 / 0.42   21 (3..8) 0.34 / 0.37   30 (3..8) 1.16 / 5.66   30 (12..14) 30.3 / 11.2
+    //   FP32  26 (3..26) 4.15 / 2.18   26 (3..12) 1.60 / 1.31  28 (3..12) 3.20 / 3.67
+    const int h = N - kCubeSuffix, kmax = cube_kmax(f32, sel->kmax);
+    double factor = 0.0, table = 4e4;
+    for (int k = sel->kmin; k <= kmax; ++k) {
+        const double n = (double)binom_u64(N, k);
+        factor += n * (f32 ? (k <= 12 ? 0.05 : 0.07) : (k <= kF64LaneMax ? 0.09 : 2.7));
+        table += n * 0.027;
+    }
+    for (int p = 0; p <= h && p <= kmax; ++p) table += 6.0 * (double)binom_u64(h, p);
+    return factor > 1.15 * table;
 }
 
 size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32) { return cube_mem(N, D, kmin, kmax, f32).total; }
