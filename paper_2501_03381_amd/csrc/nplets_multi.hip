@@ -509,16 +509,36 @@ struct MultiShape {
     bool staged[kMaxClasses];
 };
 
-MultiShape multi_shape(const thoi_eval_opts* o)
+// A class is staged from kStageMin n-plets on, four workgroups per CU with one tile each.  Below, lanes of
+// twelve n-plets one after the other leave the chip idle: 64 datasets of 8..20 variables, orders 3..6
+// (0.7 M n-plets): 42 us as in the other classes, 52 staged; 256 of 10..40, orders 3..5 (44 M): 482 and 289.
+constexpr int64_t kStageMin = (int64_t)1024 * kTile * kStageS;
+
+MultiShape multi_shape(const int32_t* N_d, int64_t D, int kmin, int kmax, const thoi_eval_opts* o)
 {
     MultiShape sh{};
     const bool f64 = o->precision == THOI_FP64;
     const KClass* c = f64 ? classes_for<double>(sh.ncls) : classes_for<float>(sh.ncls);
     for (int i = 0; i < sh.ncls; ++i) {
         sh.cls[i] = c[i];
-        sh.staged[i] = !f64 && o->out_dtype == THOI_DTYPE_F32 && staged_class<float>(c[i].hi, o->reduce != nullptr);
+        if (!f64 && o->out_dtype == THOI_DTYPE_F32 && staged_class<float>(c[i].hi, o->reduce != nullptr)) {
+            int64_t n = 0, of[THOI_MAX_N_RANGE + 1];       // n-plets of a dataset, by its size
+            for (int64_t& x : of) x = -1;
+            for (int64_t d = 0; d < D && n < kStageMin; ++d) {
+                const int N = N_d[d];
+                if (N < 1 || N > THOI_MAX_N_RANGE) continue;
+                if (of[N] < 0) {
+                    of[N] = 0;
+                    for (int k = kmin > c[i].lo ? kmin : c[i].lo; k <= kmax && k <= c[i].hi && k <= N; ++k)
+                        of[N] += (int64_t)binom_u64(N, k);
+                }
+                n += of[N];
+            }
+            sh.staged[i] = n >= kStageMin;
+        }
         sh.S[i] = sh.staged[i] ? kStageS : (f64 ? multi_per_lane<double>(c[i].hi) : multi_per_lane<float>(c[i].hi));
-        sh.per_unit[i] = (int64_t)kTile * sh.S[i] * default_seg_tiles(o);
+        // (a tile of a staged class is twice the others', so a unit of one tile)
+        sh.per_unit[i] = (int64_t)kTile * sh.S[i] * (sh.staged[i] && o->seg_tiles <= 0 ? 1 : default_seg_tiles(o));
     }
     return sh;
 }
@@ -561,7 +581,7 @@ int64_t class_grid(int64_t units, int grid_blocks)
 MultiWs multi_layout(const int32_t* N_d, int64_t D, int kmin, int kmax, const thoi_eval_opts* o)
 {
     MultiWs w{};
-    const MultiShape sh = multi_shape(o);
+    const MultiShape sh = multi_shape(N_d, D, kmin, kmax, o);
     int64_t units[kMaxClasses], entries[kMaxClasses], total = 0;
     multi_counts(N_d, D, kmin, kmax, sh, units, entries, &total);
     size_t off = kWsHeader;
@@ -635,7 +655,7 @@ thoi_status launch_multi(const double* Sigma, const int32_t* N_d, const int32_t*
     if (ws == nullptr || ws_bytes < w.total) return THOI_EWORKSPACE;
     char* base = static_cast<char*>(ws);
     const bool reduce = opts->reduce != nullptr;
-    const MultiShape sh = multi_shape(opts);
+    const MultiShape sh = multi_shape(N_d, D, kmin, kmax, opts);
     int64_t units[kMaxClasses], entries[kMaxClasses], total = 0;
     multi_counts(N_d, D, kmin, kmax, sh, units, entries, &total);
     int nmax = 0;

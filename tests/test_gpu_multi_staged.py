@@ -10,12 +10,13 @@ pytestmark = pytest.mark.gpu
 # datasets smaller than the order, one n-plet, partial and full rows of 64 x 12, unranking above and below 33
 # variables, the largest dataset; orders of this class alone and together with larger ones; every option
 @pytest.mark.parametrize("Ns,kmin,kmax,prec,entropy,bias", [
-    ([3, 2, 8, 9, 10, 1, 12, 17], 1, 8, "fp32_refine", True, True),
-    ([5, 40, 33, 34, 32, 31, 10, 5, 5], 3, 5, "fp32_refine", False, False),
-    ([62, 61, 3, 33], 2, 4, "fp32", True, False),
-    ([14, 15, 16, 20], 7, 12, "fp32_refine", False, True),
-    ([20, 24, 8], 8, 8, "fp32", False, False),
-    ([7], 0, 7, "fp32_refine", True, False)])
+    ([3, 2, 8, 9, 10, 25, 1, 12, 17, 25], 1, 8, "fp32_refine", True, True),
+    ([5, 40, 33, 34, 32, 31, 10, 5, 5, 40, 39, 40, 40, 40], 3, 5, "fp32_refine", False, False),
+    ([62, 61, 3, 33, 62, 62, 60, 62, 62], 2, 4, "fp32", True, False),
+    ([14, 15, 16, 20, 27, 20, 20], 7, 9, "fp32_refine", False, True),
+    ([20, 24, 8, 25, 25, 25], 8, 8, "fp32", False, False),
+    ([7, 31], 0, 7, "fp32_refine", True, False),
+    ([7, 12, 20], 0, 7, "fp32_refine", True, False)])          # too few for the buffer
 def test_staged_output_is_the_lane_output(Ns, kmin, kmax, prec, entropy, bias):
     import torch
     from paper_2501_03381_amd import api, synth
