@@ -356,9 +356,10 @@ size_t thoi_workspace_bytes(int32_t which, int64_t D, int64_t T, int32_t N,
  * Workspace with which thoi_nplets_eval may also take engines that keep a table (never less than
  * thoi_workspace_bytes(THOI_WS_EVAL, ...), which stays enough for every call): with THOI_ENGINE_AUTO,
  * a streaming reduction over whole orders (from order 3; FP64: of 21..30 variables, FP32 + refinement:
- * 26..30) then filters the n-plets with a table of log det over all subsets, 2^(N+3) bytes in FP64 and
- * 2^(N+2) in FP32 (8 and 4 GB at N = 30; several datasets at a time up to 256 MB) and, behind it, two lists
- * of the n-plets that it leaves open (1.4 GB each at N = 30), instead of factoring every n-plet.
+ * 26..30; where that is estimated to be faster) filters the n-plets with a table of log det over all
+ * subsets, 2^(N+3) bytes in FP64 and 2^(N+2) in FP32 (8 and 4 GB at N = 30; several datasets at a time
+ * up to 256 MB) and, behind it, two lists of the n-plets that it leaves open (1.4 GB each at N = 30),
+ * instead of factoring every n-plet.
  * Results are the same bit for bit.
  */
 size_t thoi_eval_workspace_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
