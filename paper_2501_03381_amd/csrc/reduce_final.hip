@@ -7,7 +7,9 @@
 // only entries up to it are collected, and they are sorted once.  Merging the segments one after
 // the other (two dependent global reads and two barriers each) took 285 us for the 236 segments
 // of an objective over 60,458 n-plets with K = 100; the whole call of 64 datasets and that objective
-// went from 482 to 215 us, the FP64 reduction of 25 variables from 4.70 to 4.31 ms.
+// went from 482 to 215 us, the FP64 reduction of 25 variables from 4.70 to 4.31 ms.  The threshold is a
+// (key, index) pair: by the key alone every entry of equal values was collected and sorted (a million
+// equal values, K = 100: 8.66 ms, 0.39 so; distinct ones 0.27).
 #include "radix_pick.hpp"
 #include "reduce_common.hpp"
 
@@ -23,10 +25,12 @@ static_assert(kFinBuf >= kFinWaves * kRedMaxK && kFinBuf >= kFinThreads, "one ro
 struct RedFinal {
     RedItem list[2][kRedMaxK];                   // the running list, double-buffered
     RedItem buf[kFinBuf];                        // collected entries
-    uint64_t head[kFinSegs];                     // matching segments: one key of each ...
-    uint32_t seg[kFinSegs];                      // ... and its slot
+    uint64_t head[kFinSegs];                     // matching segments: the first key of each ...
+    int64_t head_g[kFinSegs];                    // ... its index ...
+    uint32_t seg[kFinSegs];                      // ... and the segment's slot
     uint32_t rh[256];                            // radix selection
-    uint64_t thr;                                // entries with a larger key are not needed
+    uint64_t thr;                                // entries behind (thr, thr_g) are not needed
+    int64_t thr_g;
     uint32_t prefix;
     int cur, nbuf, nseg, rank;
 };
@@ -59,8 +63,8 @@ __device__ __forceinline__ void red_final_flush(RedFinal& S, int K)
         S.list[c ^ 1][i] = red_merge_at(S.list[c], K, S.buf, n < K ? n : K, i);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint64_t t = S.list[c ^ 1][K - 1].k;
-        if (t < S.thr) S.thr = t;
+        const RedItem t = S.list[c ^ 1][K - 1];
+        if (red_less(t.k, t.g, S.thr, S.thr_g)) { S.thr = t.k; S.thr_g = t.g; }
         S.cur = c ^ 1;
         S.nbuf = 0;
     }
@@ -101,6 +105,37 @@ __device__ __forceinline__ uint64_t red_final_select(RedFinal& S, int n, int K)
     return ((uint64_t)S.prefix << 32) | 0xffffffffull;
 }
 
+// Whole workgroup: the segments [r, n) whose head can still enter, moved to the front; their number.
+__device__ __forceinline__ int red_final_repack(RedFinal& S, int r, int n)
+{
+    constexpr int kU = kFinSegs / kFinThreads;
+    uint64_t h[kU];
+    int64_t g[kU];
+    uint32_t s[kU];
+    bool on[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const int j = r + (int)threadIdx.x + u * kFinThreads;
+        on[u] = j < n;
+        h[u] = on[u] ? S.head[j] : 0;
+        g[u] = on[u] ? S.head_g[j] : 0;
+        s[u] = on[u] ? S.seg[j] : 0;
+        on[u] = on[u] && !red_less(S.thr, S.thr_g, h[u], g[u]);
+    }
+    if (threadIdx.x == 0) S.nseg = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+        if (on[u]) {
+            const int j = atomicAdd(&S.nseg, 1);
+            S.head[j] = h[u];
+            S.head_g[j] = g[u];
+            S.seg[j] = s[u];
+        }
+    __syncthreads();
+    return S.nseg;
+}
+
 __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader* hdr)
 {
     __shared__ RedFinal S;
@@ -117,19 +152,20 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
     if (tid == 0) { S.cur = 0; S.nbuf = 0; S.nseg = 0; }
     __syncthreads();
     if (tid == 0) {
-        uint64_t t = S.list[0][K - 1].k;
+        S.thr = S.list[0][K - 1].k;
+        S.thr_g = S.list[0][K - 1].g;
         if (red.bound) {
             // the tightest K-th key that a segment of this (d, k) has published
             const uint64_t b = ~(uint64_t)red.bound[((int64_t)d * (red.kmax + 1) + k) * 2 + l];
-            t = b < t ? b : t;
+            if (b < S.thr) { S.thr = b; S.thr_g = kGEmpty; }
         }
-        S.thr = t;
     }
     __syncthreads();
     const uint32_t nseg = min(hdr->seg_next, red.seg_cap);
     for (uint32_t s0 = 0; s0 < nseg;) {
         // the next segments of this (d, k) whose head can still enter, up to kFinSegs of them
         const uint64_t thr = S.thr;
+        const int64_t thr_g = S.thr_g;
         constexpr int kU = kFinSegs / kFinThreads;
         SegHdr h[kU];
 #pragma unroll
@@ -142,9 +178,11 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
             const uint32_t s = s0 + tid + u * kFinThreads;
             if (h[u].d == d && h[u].k == k) {
                 const uint64_t key = red.seg_key[((int64_t)s * 2 + l) * K];
-                if (key != kKeyEmpty && key <= thr) {
+                const int64_t g = red.seg_g[((int64_t)s * 2 + l) * K];
+                if (key != kKeyEmpty && !red_less(thr, thr_g, key, g)) {
                     const int j = atomicAdd(&S.nseg, 1);
                     S.head[j] = key;
+                    S.head_g[j] = g;
                     S.seg[j] = s;
                 }
             }
@@ -156,7 +194,7 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
             // K heads reach this key, so K entries do: a larger one is not needed, nor is a segment
             // with a larger head
             const uint64_t t = red_final_select(S, n, K);
-            if (tid == 0 && t < S.thr) S.thr = t;
+            if (tid == 0 && t < S.thr) { S.thr = t; S.thr_g = kGEmpty; }
         } else if (n > kFinWaves) {
             // fewer segments than K: the j-th entries of all of them with n * j >= K
             const int j = (K + n - 1) / n;
@@ -171,7 +209,7 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
             __syncthreads();
             if (lane == 0) atomicMax(reinterpret_cast<unsigned long long*>(&S.head[0]), (unsigned long long)worst);
             __syncthreads();
-            if (tid == 0 && S.head[0] < S.thr) S.thr = S.head[0];
+            if (tid == 0 && S.head[0] < S.thr) { S.thr = S.head[0]; S.thr_g = kGEmpty; }
         }
         __syncthreads();
         const bool sel = n >= K && n > kFinWaves;
@@ -179,7 +217,14 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
         for (int r = 0; r < n; r += kFinWaves) {
             const int nb = S.nbuf;
             __syncthreads();                     // every thread has read nbuf before the next append
-            if (nb + kFinWaves * K > kFinBuf) red_final_flush(S, K);
+            if (nb + kFinWaves * K > kFinBuf) {
+                red_final_flush(S, K);
+                if (sel) {
+                    n = red_final_repack(S, r, n);
+                    r = 0;
+                    if (n == 0) break;           // uniform
+                }
+            }
             const uint64_t t = S.thr;
             const int j = r + wave;
             if (j < n && !(sel && S.head[j] > t)) {
@@ -187,9 +232,13 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
                 for (int i0 = 0; i0 < K; i0 += 64) {
                     const int i = i0 + lane;
                     const uint64_t key = i < K ? red.seg_key[e0 + i] : kKeyEmpty;
-                    const bool want = key != kKeyEmpty && key <= t;
-                    red_final_append(S, want, key, want ? red.seg_g[e0 + i] : 0);
-                    if (__ballot(want) != ~0ull) break;      // sorted: nothing further on is smaller
+                    bool want = key != kKeyEmpty && key <= t;
+                    const bool all = __ballot(want) == ~0ull;
+                    const int64_t g = want ? red.seg_g[e0 + i] : 0;
+                    // (no wait for the index where no key ties with the threshold's)
+                    if (__ballot(want && key == t)) want = want && (key < t || g <= S.thr_g);
+                    red_final_append(S, want, key, g);
+                    if (!all) break;                         // sorted: nothing further on is smaller
                 }
             }
             __syncthreads();
@@ -204,6 +253,7 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
     for (uint32_t b0 = 0; b0 < nlate; b0 += kFinBuf) {
         red_final_flush(S, K);
         const uint64_t t = S.thr;
+        const int64_t thr_g = S.thr_g;
         LateEntry e[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -213,7 +263,7 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const uint64_t key = red_list_key(l, e[u].v);
-            red_final_append(S, e[u].d == d && e[u].k == k && key <= t, key, e[u].g);
+            red_final_append(S, e[u].d == d && e[u].k == k && !red_less(t, thr_g, key, e[u].g), key, e[u].g);
         }
     }
     red_final_flush(S, K);

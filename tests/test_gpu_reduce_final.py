@@ -38,3 +38,24 @@ def test_final_merge_is_an_exact_selection(B, K, ties):
         n = len(val)
         assert np.array_equal(tg[0, 0, l, :n], keep[idx]) and np.array_equal(tv[0, 0, l, :n], val)
         assert np.all(tg[0, 0, l, n:] == -1)
+
+
+def test_equal_values_cost_about_what_distinct_ones_do():
+    """Of equal values the lowest indices are kept: the merge must not collect the rest of them (it sorted every
+    segment's K entries: 25 times as long as with distinct values)."""
+    import torch
+    from paper_2501_03381_amd import api
+    B, t = 4096 * 256, {}
+    for name, v in (("distinct", torch.randn(1, B, dtype=torch.float64, device="cuda")),
+                    ("equal", torch.zeros(1, B, dtype=torch.float64, device="cuda"))):
+        print(f"[gpu-case] final merge of {name} values", flush=True)
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            api.objective(v, "mean", write=False, topk=100)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        t[name] = best
+    assert t["equal"] < 4 * t["distinct"], t
