@@ -34,6 +34,8 @@
 #include "nplets_cube.hpp"
 #include "radix_pick.hpp"
 
+#include <cmath>
+
 namespace thoi {
 namespace {
 
@@ -872,6 +874,33 @@ CubeMem cube_mem(int N, int64_t D, int kmin, int kmax, bool f32)
 
 int cube_kmax(bool f32, int kmax) { return f32 && kmax > kF32LaneMax ? kF32LaneMax : kmax; }
 
+// Estimated times in ns in FP64, D datasets, fitted to 369 pairs of timings (21..30 variables, D = 1, 4 and 16, single orders
+// and ranges).  A factorisation per n-plet: up to order 12 (prefix sharing, the better the more tails a prefix
+// has) 0.036 + 0.13 e with e = 2^-((N - 21) / 2.5), a tenth more at 12; then 0.077 + 0.19 e; from 15 on 0.22, from 19
+// on (two per wavefront) 2.9; 50,000 a call, with orders above 18 another 350,000, the latency of their lanes.
+// The table: 4.6 per row and 0.53 for each order that passes over it, and 4 for each order that kmin lies above
+// h (the rows of many members, which hold the n-plets, are then few and close together), 0.011 per n-plet,
+// 95,000 per dataset (they are filtered one after the other) and 155,000 a call.  A factorisation per
+// n-plet / the table, ms; the choice is the slower one of the two by 5% at most in 4 of the 369:
+//   21 (3..21) 0.74 / 0.35   21 (3..10) 0.19 / 0.30   24 (3..9) 0.30 / 0.40    24 (3..10) 0.52 / 0.46
+//   25 (3..25) 4.16 / 1.08   25 (12..12) 0.45 / 0.46  27 (3..10) 1.03 / 1.52   30 (3..12) 8.94 / 11.9
+//   D = 4:   21 (3..21) 1.59 / 0.83   25 (3..10) 2.36 / 2.43   25 (19..25) 3.20 / 3.75   27 (21..27) 5.92 / 7.66
+//   D = 16:  21 (3..21) 6.11 / 2.91   21 (3..9) 1.61 / 1.97    24 (3..9) 4.04 / 4.78     23 (14..23) 7.44 / 4.13
+bool cube_faster_f64(int32_t N, int64_t D, int kmin, int kmax)
+{
+    const int h = N - kCubeSuffix;
+    const double e = std::exp2(-(N - 21) / 2.5), low = 0.036 + 0.13 * e, mid = 0.077 + 0.19 * e;
+    double n = 0.0, factor = (5e4 + (kmax > kF64LaneMax ? 3.5e5 : 0.0)) / (double)D;
+    for (int k = kmin; k <= kmax; ++k) {
+        const double c = (double)binom_u64(N, k);
+        n += c;
+        factor += c * (k < 12 ? low : k == 12 ? 1.1 * low : k <= 14 ? mid : k <= kF64LaneMax ? 0.22 : 2.9);
+    }
+    const double row = 4.6 + 0.53 * (kmax - kmin + 1) + (kmin > h ? 4.0 * (kmin - h) : 0.0);
+    const double table = 1.55e5 / (double)D + 9.5e4 + row * (double)(int64_t(1) << h) + 0.011 * n;
+    return factor > 1.04 * table;
+}
+
 bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_opts* opts)
 {
     if (sel->mode != THOI_SEL_RANGE || !opts->reduce || D < 1) return false;
@@ -884,17 +913,17 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
     int64_t all = 0;
     for (int k = sel->kmin; k <= sel->kmax; ++k) all += (int64_t)binom_u64(N, k);
     if (sel->g_begin != 0 || sel->g_count != all) return false;
-    // Estimated times in ns.  A factorisation per n-plet (prefix sharing and the pair engine in FP64, the
-    // lane engine's classes in FP32): 0.09 up to order 18 and 2.7 above; 0.05 up to order 12, 0.07 above.
-    // The table: 6 per row of up to kmax members, whatever sizes are needed, 0.027 per n-plet, 40,000 for
-    // the additional launches.  Measured, a factorisation per n-plet / the table, ms (orders):
-    //   FP64  21 (3..21) 1.10 / 0.42   21 (3..8) 0.34 / 0.37   30 (3..8) 1.16 / 5.66   30 (12..14) 30.3 / 11.2
-    //   FP32  26 (3..26) 4.15 / 2.18   26 (3..12) 1.60 / 1.31  28 (3..12) 3.20 / 3.67
-    const int h = N - kCubeSuffix, kmax = cube_kmax(f32, sel->kmax);
+    if (!f32) return cube_faster_f64(N, D, sel->kmin, sel->kmax);
+    // Estimated times in ns, FP32 + refinement.  A factorisation per n-plet: 0.05 up to order 12, 0.07 above.  The
+    // table: 6 per row of up to kmax members, whatever sizes are needed, 0.027 per n-plet, 40,000 for the
+    // additional launches.  Measured, a factorisation per n-plet / the table, ms (orders, D datasets):
+    //   26 (3..26) 3.76 / 1.92   26 (3..12) 1.25 / 1.18   26 (3..10) 0.55 / 1.02   26 (18..26) 0.53 / 1.04
+    //   28 (3..28) 14.5 / 6.80   28 (3..12) 2.74 / 3.48   28 (12..14) 4.68 / 2.84  D = 4: 26 (3..26) 13.6 / 7.42
+    const int h = N - kCubeSuffix, kmax = cube_kmax(true, sel->kmax);
     double factor = 0.0, table = 4e4;
     for (int k = sel->kmin; k <= kmax; ++k) {
         const double n = (double)binom_u64(N, k);
-        factor += n * (f32 ? (k <= 12 ? 0.05 : 0.07) : (k <= kF64LaneMax ? 0.09 : 2.7));
+        factor += n * (k <= 12 ? 0.05 : 0.07);
         table += n * 0.027;
     }
     for (int p = 0; p <= h && p <= kmax; ++p) table += 6.0 * (double)binom_u64(h, p);

@@ -11,7 +11,9 @@ namespace thoi {
 constexpr int kCubeSuffix = 10;                       // variables of a table row
 constexpr int kCubeRow = 1 << kCubeSuffix;
 constexpr int kCubeMinN = 21, kCubeMaxN = 30;
-constexpr int kCubeMinN32 = 26;                       // FP32 + refinement
+constexpr int kCubeMinN32 = 26;                       // FP32 + refinement (a factorisation per n-plet / the table, ms, all
+                                                      // orders: N = 22 0.51 / 0.45, 23 0.72 / 0.54, 24 1.16 / 0.75, 25
+                                                      // 2.06 / 1.12, 26 3.76 / 1.92: the line could lie lower)
 
 // The orders of a call and the rows of one launch: block (chunk c, order i) takes order p[i].k of the
 // rows [row0 + c * per, row0 + (c + 1) * per).
