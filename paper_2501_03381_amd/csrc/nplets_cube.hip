@@ -932,10 +932,16 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
 
 size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32) { return cube_mem(N, D, kmin, kmax, f32).total; }
 
-int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax)
+int64_t cube_segments(int32_t N, int kmin, int kmax, bool f32)
 {
-    const int64_t rows = int64_t(1) << (N - kCubeSuffix);
-    return (rows >> filter_bits(N)) * (kmax - kmin + 1) * kVerifyBlocks * D;
+    // a workgroup of the evaluation without an open n-plet leaves none
+    const int64_t blocks = int64_t(1) << (N - kCubeSuffix - filter_bits(N));
+    int64_t n = 0;
+    for (int k = kmin; k <= kmax; ++k) {
+        const int64_t per = f32 || k <= kF64LaneMax ? kTile : kTile / 32, most = (open_cap(N, k) + per - 1) / per;
+        n += blocks * (most < kVerifyBlocks ? most : kVerifyBlocks);
+    }
+    return n;
 }
 
 namespace {

@@ -41,8 +41,8 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
 int cube_kmax(bool f32, int kmax);
 // Bytes behind the segments and the queue: tables, sample keys and open lists.
 size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32);
-// Segments the reduction leaves (an upper bound).
-int64_t cube_segments(int32_t N, int64_t D, int kmin, int kmax);
+// Segments the reduction of a dataset leaves (an upper bound).
+int64_t cube_segments(int32_t N, int kmin, int kmax, bool f32);
 // beside (or empty): launches of the call that do not touch the table, put on a stream beside the first
 // table's build.  serial: everything on s.
 void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,

@@ -431,7 +431,7 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         if (cube) {
             const bool f32 = opts->precision != THOI_FP64;
             // orders above the cube engine's stay with the pair engine's plan
-            segs = cube_segments(N, D, sel->kmin, cube_kmax(f32, sel->kmax)) + P.wblk * D;
+            segs = (cube_segments(N, sel->kmin, cube_kmax(f32, sel->kmax), f32) + (f32 ? P.wblk : 0)) * D;
         }
         w.seg_cap = (uint32_t)(segs > 0 ? segs : 1);
         w.seg_key_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);

@@ -367,3 +367,11 @@ def _reduce_bytes(B, prec, N, kmin, kmax, D, K=100):
 def test_subset_table_only_where_it_is_faster_fp64(B, N, kmin, kmax, D, table):
     least, full = _reduce_bytes(B, B.THOI_FP64, N, kmin, kmax, D)
     assert (full > least) == table
+
+
+@pytest.mark.parametrize("prec,N,D", [("THOI_FP64", 21, 5000), ("THOI_FP64", 23, 1000), ("THOI_FP32_REFINE", 26, 500)])
+def test_subset_table_asks_for_little_beside_its_tables(B, prec, N, D):
+    """Many datasets: beside the tables (256 MB at a time) and their open lists no more than without the table, give
+    or take a quarter."""
+    least, full = _reduce_bytes(B, getattr(B, prec), N, 3, N, D)
+    assert full < 1.25 * least + (1 << 30)
