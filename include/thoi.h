@@ -359,7 +359,8 @@ size_t thoi_workspace_bytes(int32_t which, int64_t D, int64_t T, int32_t N,
  * 26..30; where that is estimated to be faster) filters the n-plets with a table of log det over all
  * subsets, 2^(N+3) bytes in FP64 and 2^(N+2) in FP32 (8 and 4 GB at N = 30; several datasets at a time
  * up to 256 MB) and, behind it, two lists of the n-plets that it leaves open (1.4 GB each at N = 30),
- * instead of factoring every n-plet.
+ * instead of factoring every n-plet.  FP32 samples each dataset first and factors every n-plet where the
+ * table would leave too many open.
  * Results are the same bit for bit.
  */
 size_t thoi_eval_workspace_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);

@@ -32,6 +32,7 @@
 // Taking the table's values themselves (no second evaluation) measured 1.05 ms at N = 25, with errors
 // against 64-bit references of 1e-14 instead of 2e-15.
 #include "nplets_cube.hpp"
+#include "nplets_cube_margin.hpp"
 #include "radix_pick.hpp"
 
 #include <cmath>
@@ -105,7 +106,7 @@ __device__ __forceinline__ void cube_wave_sync()
 // Entries of the table.  FP64: the value.  FP32: the filter's margin is a thousand times an FP32 rounding,
 // so the value in fixed point, 2^-25 each (half the bytes, exact sums); kFixBad: not positive definite
 // or below -64.
-constexpr double kFixScale = 33554432.0;                // 2^25
+constexpr double kFixScale = 33554432.0;                // 2^25 (values inside +-kFixMax)
 constexpr int32_t kFixBad = 0x7fffffff;
 template <bool F32>
 struct TableOf { typedef double T; };
@@ -117,7 +118,7 @@ using Tab = typename TableOf<F32>::T;
 __device__ __forceinline__ void encode(double ld, double& e) { e = ld; }
 __device__ __forceinline__ void encode(double ld, int32_t& e)
 {
-    e = ld > -63.5 && ld < 63.5 ? __double2int_rn(ld * kFixScale) : kFixBad;
+    e = ld > -kFixMax && ld < kFixMax ? __double2int_rn(ld * kFixScale) : kFixBad;
 }
 __device__ __forceinline__ double decode(double e) { return e; }
 __device__ __forceinline__ double decode(int32_t e) { return e == kFixBad ? __builtin_nan("") : (double)e * (1.0 / kFixScale); }
@@ -194,12 +195,14 @@ __device__ __forceinline__ void cube_walk(const double (&s)[(kCubeSuffix - V) * 
 }
 
 // grid (ceil(2^h / 16), datasets of the group), block kBuildThreads: rows P of the table of dataset
-// d0 + blockIdx.y, kBuildRows per wavefront.  Bit h - 1 - v of P is variable v.  Rows with more than kmax
-// members are not needed.
+// d0 + blockIdx.y (those that take is null or nonzero for), kBuildRows per wavefront.  Bit h - 1 - v of P is
+// variable v.  Rows with more than kmax members are not needed.
 template <bool F32>
 __global__ __launch_bounds__(kBuildThreads) void k_cube_build(const double* __restrict__ Sigma, int N, int64_t d0,
-                                                              int kmax, Tab<F32>* __restrict__ table)
+                                                              int kmax, const uint32_t* __restrict__ take,
+                                                              Tab<F32>* __restrict__ table)
 {
+    if (take && !take[d0 + blockIdx.y]) return;                        // uniform
     extern __shared__ __align__(16) unsigned char smem[];
     double* sR = reinterpret_cast<double*>(smem);                      // [N][N]
     double* sIsd = sR + N * N;                                         // [N]
@@ -456,42 +459,6 @@ struct LeaveOneOut {
     }
 };
 
-// How far Omega and the VIFs of a factorisation per n-plet (FP32 or FP64) may be from the table's.  With
-// E the perturbation of R_S by rounding it and factoring it (entries of a few units u = 2^-24 or 2^-53),
-// log det moves by tr(R_S^-1 E) and log a_j by (R_S^-1 E R_S^-1)_jj / a_j, to first order; |R_S^-1|_ij
-// <= sqrt(a_i a_j), so both are at most |E| (sum sqrt a)^2 <= |E| k sum a.  Taken: 4 u k sum_j a_j in FP32
-// (about 200 times what the engines differ by on the test systems) and 64 u k sum_j a_j in FP64, where a
-// wide margin costs nothing, plus the rounding of the measures and of the table's sum (k terms of up to
-// |ld| = 2 |TC|, each addition to within u of a sum of up to k |ld|; fixed point: half a unit in each of up
-// to 25 entries).
-struct Margin {
-    double rel;              // of log det, log a_j, and relative of a_j
-    double round;
-    int vif;                 // FP32: 0 below the refinement threshold, 1 may be on either side, 2 above
-    __device__ __forceinline__ double value(double TC, double DTC) const
-    {
-        return rel + round * (fabs(TC) + fabs(DTC) + 1.0);
-    }
-};
-template <bool F32>
-__device__ __forceinline__ Margin margin_of(int k, double ld, float mx, float ex, float tau)
-{
-    Margin m;
-    if constexpr (F32) {
-        const float rel = 4.0f * 5.9604645e-8f * (float)k * ex;
-        const float v = __builtin_amdgcn_exp2f(mx * 1.442695041f), d = rel + 1e-5f + 2e-6f * fabsf((float)ld);
-        m.rel = (double)rel + 4e-7;
-        m.round = 2.4e-7;
-        m.vif = !(v * (1.0f + d) < tau) ? (v > tau * (1.0f + d) ? 2 : 1) : 0;
-        if (!(rel < 0.25f)) m.vif = m.vif == 0 ? 1 : m.vif;
-    } else {
-        m.rel = 64.0 * 1.1102230246251565e-16 * k * (double)ex;
-        m.round = 4e-15 + 4.5e-16 * (double)(k * k);
-        m.vif = 0;
-    }
-    return m;
-}
-
 // ------------------------------------------------------------------------------------------------
 // Admission bounds before the reduction.  A workgroup that starts with empty lists inserts almost
 // every value of its first iterations, at about 7,000 cycles per insertion: so kSampleGroups
@@ -507,14 +474,17 @@ constexpr int kSamplePer = 8;                          // pieces per wavefront
 constexpr int kSampleGroups = 8;
 constexpr uint32_t kSamplePieces = kSampleThreads / 64 * kSamplePer * kSampleGroups;
 
-// grid (kSampleGroups, orders, datasets of the group): sbound[dataset of the group][order][group][2].
+// grid (kSampleGroups, orders, datasets of the group): sbound[dataset of the group][order][group][2].  take: by
+// dataset of the group, or null.
 // The values are taken at the unfavourable end of what the factorisation may make of them; FP32:
 // n-plets near or above the refinement threshold are left out.
 template <bool F32>
-__global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, CubeTable tab, int K, int64_t d0,
+__global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, CubeTable tab, int K,
+                                                                const uint32_t* __restrict__ take,
                                                                 const Tab<F32>* __restrict__ table,
                                                                 uint64_t* __restrict__ sbound)
 {
+    if (take && !take[blockIdx.z]) return;                             // uniform
     __shared__ uint32_t sbin[kCubeMaxN * (kCubeMaxN + 1)];
     __shared__ uint16_t snbr[kCubeSuffix * kCubeRow / 2];
     __shared__ uint32_t rh[256];
@@ -602,10 +572,11 @@ __global__ __launch_bounds__(kSampleThreads) void k_cube_sample(EvalArgs a, Cube
 }
 
 // grid (orders, datasets of the group), block 64: the bound of each list from its groups' keys.
-__global__ void k_cube_bounds(CubeTable tab, RedArgs red, int64_t d0, const uint64_t* __restrict__ sbound)
+__global__ void k_cube_bounds(CubeTable tab, RedArgs red, int64_t d0, const uint32_t* __restrict__ take,
+                              const uint64_t* __restrict__ sbound)
 {
     const int l = threadIdx.x;
-    if (l >= 2) return;
+    if (l >= 2 || (take && !take[d0 + blockIdx.y])) return;
     const uint64_t* b = sbound + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kSampleGroups * 2 + l;
     uint64_t worst = 0;
     for (int g = 0; g < kSampleGroups; ++g) worst = b[2 * g] > worst ? b[2 * g] : worst;
@@ -627,7 +598,7 @@ __device__ __forceinline__ void flush_open(const CubeOpen& o, int k, const uint3
     cube_wave_sync();
 }
 
-// grid (8 ceil(chunks / 8) orders), block 256: dataset d0, its table.
+// grid (8 ceil(chunks / 8) orders), block 256: dataset d0, its table.  take: as for the build.
 //
 // The results are those of one factorisation per n-plet bit for bit (list values and indices, counts,
 // what is refined), so the table's values only decide where the factorisation's cannot differ: an n-plet
@@ -636,8 +607,9 @@ __device__ __forceinline__ void flush_open(const CubeOpen& o, int k, const uint3
 // left open and evaluated by k_cube_verify.
 template <bool F32>
 __global__ __launch_bounds__(256) void k_cube_filter(EvalArgs a, CubeTable tab, RedArgs red, CubeOpen opn, int64_t d0,
-                                                     const Tab<F32>* __restrict__ table)
+                                                     const uint32_t* __restrict__ take, const Tab<F32>* __restrict__ table)
 {
+    if (take && !take[d0]) return;                                     // uniform
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t sopen[4 * kOpenBuf];
     __shared__ uint16_t smask[kCubeRow];
@@ -874,7 +846,29 @@ CubeMem cube_mem(int N, int64_t D, int kmin, int kmax, bool f32)
 
 int cube_kmax(bool f32, int kmax) { return f32 && kmax > kF32LaneMax ? kF32LaneMax : kmax; }
 
-// Estimated times in ns in FP64, D datasets, fitted to 369 pairs of timings (21..30 variables, D = 1, 4 and 16, single orders
+// Estimated times in ns, FP32 + refinement.  A factorisation per n-plet: 0.05 up to order 12, 0.07 above.  The
+// table: 6 per row of up to kmax members, whatever sizes are needed, 0.027 per n-plet, 40,000 for the
+// additional launches; 1.3 times its share for an open n-plet, which is evaluated by itself.  Measured, a
+// factorisation per n-plet / the table, ms (orders, D datasets):
+//   26 (3..26) 3.76 / 1.92   26 (3..12) 1.25 / 1.18   26 (3..10) 0.55 / 1.02   26 (18..26) 0.53 / 1.04
+//   28 (3..28) 14.5 / 6.80   28 (3..12) 2.74 / 3.48   28 (12..14) 4.68 / 2.84  D = 4: 26 (3..26) 13.6 / 7.42
+CubeCost cube_cost(int32_t N, int kmin, int kmax)
+{
+    CubeCost c{};
+    const int h = N - kCubeSuffix;
+    double table = 4e4;
+    for (int k = kmin; k <= kmax; ++k) {
+        const double n = (double)binom_u64(N, k), per = k <= 12 ? 0.05 : 0.07;
+        c.factor[k] = (float)(n * per);
+        c.open[k] = (float)(n * 1.3 * per);
+        table += n * 0.027;
+    }
+    for (int p = 0; p <= h && p <= kmax; ++p) table += 6.0 * (double)binom_u64(h, p);
+    c.table = (float)table;
+    return c;
+}
+
+// The same for D datasets in FP64, fitted to 369 pairs of timings (21..30 variables, D = 1, 4 and 16, single orders
 // and ranges).  A factorisation per n-plet: up to order 12 (prefix sharing, the better the more tails a prefix
 // has) 0.036 + 0.13 e with e = 2^-((N - 21) / 2.5), a tenth more at 12; then 0.077 + 0.19 e; from 15 on 0.22, from 19
 // on (two per wavefront) 2.9; 50,000 a call, with orders above 18 another 350,000, the latency of their lanes.
@@ -914,20 +908,11 @@ bool cube_wanted(int32_t N, int64_t D, const thoi_nplets* sel, const thoi_eval_o
     for (int k = sel->kmin; k <= sel->kmax; ++k) all += (int64_t)binom_u64(N, k);
     if (sel->g_begin != 0 || sel->g_count != all) return false;
     if (!f32) return cube_faster_f64(N, D, sel->kmin, sel->kmax);
-    // Estimated times in ns, FP32 + refinement.  A factorisation per n-plet: 0.05 up to order 12, 0.07 above.  The
-    // table: 6 per row of up to kmax members, whatever sizes are needed, 0.027 per n-plet, 40,000 for the
-    // additional launches.  Measured, a factorisation per n-plet / the table, ms (orders, D datasets):
-    //   26 (3..26) 3.76 / 1.92   26 (3..12) 1.25 / 1.18   26 (3..10) 0.55 / 1.02   26 (18..26) 0.53 / 1.04
-    //   28 (3..28) 14.5 / 6.80   28 (3..12) 2.74 / 3.48   28 (12..14) 4.68 / 2.84  D = 4: 26 (3..26) 13.6 / 7.42
-    const int h = N - kCubeSuffix, kmax = cube_kmax(true, sel->kmax);
-    double factor = 0.0, table = 4e4;
-    for (int k = sel->kmin; k <= kmax; ++k) {
-        const double n = (double)binom_u64(N, k);
-        factor += n * (k <= 12 ? 0.05 : 0.07);
-        table += n * 0.027;
-    }
-    for (int p = 0; p <= h && p <= kmax; ++p) table += 6.0 * (double)binom_u64(h, p);
-    return factor > 1.15 * table;
+    const int kmax = cube_kmax(true, sel->kmax);
+    const CubeCost c = cube_cost(N, sel->kmin, kmax);
+    double factor = 0.0;
+    for (int k = sel->kmin; k <= kmax; ++k) factor += (double)c.factor[k];
+    return factor > 1.15 * (double)c.table;
 }
 
 size_t cube_bytes(int32_t N, int64_t D, int kmin, int kmax, bool f32) { return cube_mem(N, D, kmin, kmax, f32).total; }
@@ -947,8 +932,8 @@ int64_t cube_segments(int32_t N, int kmin, int kmax, bool f32)
 namespace {
 
 template <bool F32>
-void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool serial, void* mem,
-            const std::function<void(hipStream_t)>& beside, hipStream_t s)
+void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool serial, const CubeGate& gate, void* mem,
+            const std::function<void(hipStream_t)>& beside, const std::function<void(const FanScope&)>& rest, hipStream_t s)
 {
     static_assert(sizeof(kSuffixHost.nbr) == kCubeSuffix * kCubeRow, "one neighbour per element");
     const int64_t rows = int64_t(1) << (a.N - kCubeSuffix);
@@ -965,6 +950,7 @@ void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool seri
         open[i].list = reinterpret_cast<uint32_t*>(base + m.list[i]);
         open[i].cnt = reinterpret_cast<uint32_t*>(base + m.cnt + 256 * i);
     }
+    if (gate.take) cube_gate_launch(a, tab, red, gate, cube_cost(a.N, kmin, kmax), s);
     for (int64_t d0 = 0; d0 < a.D; d0 += group) {
         const int64_t nd = d0 + group < a.D ? group : a.D - d0;
         {
@@ -973,12 +959,12 @@ void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool seri
             if (two) beside(fan.stream(1));
             const int64_t nb = (rows + kBuildWaves * kBuildRows - 1) / (kBuildWaves * kBuildRows);
             hipLaunchKernelGGL(k_cube_build<F32>, dim3((unsigned)nb, (unsigned)nd), dim3(kBuildThreads), build_lds_bytes(a.N),
-                               fan.stream(0), a.Sigma, a.N, d0, kmax, table);
+                               fan.stream(0), a.Sigma, a.N, d0, kmax, gate.take, table);
         }
         if (red.topk > 0) {
             hipLaunchKernelGGL(k_cube_sample<F32>, dim3(kSampleGroups, (unsigned)tab.n, (unsigned)nd), dim3(kSampleThreads), 0, s, a, tab,
-                               red.topk, d0, table, sbound);
-            hipLaunchKernelGGL(k_cube_bounds, dim3((unsigned)tab.n, (unsigned)nd), dim3(64), 0, s, tab, red, d0, sbound);
+                               red.topk, gate.take ? gate.take + d0 : nullptr, table, sbound);
+            hipLaunchKernelGGL(k_cube_bounds, dim3((unsigned)tab.n, (unsigned)nd), dim3(64), 0, s, tab, red, d0, gate.take, sbound);
         }
         // one dataset at a time, block of rows after block of rows, each evaluated beside the next filter
         const int64_t steps = nd * (rows / step);
@@ -989,21 +975,22 @@ void launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool seri
                 tab.row0 = (int32_t)(i % (rows / step) * step);
                 ws_clear(open[i & 1].cnt, 256, fan.stream(0));
                 hipLaunchKernelGGL(k_cube_filter<F32>, dim3((unsigned)blocks), dim3(256), filter_lds_bytes(red), fan.stream(0), a, tab, red,
-                                   open[i & 1], d0 + e, table + (e << a.N));
+                                   open[i & 1], d0 + e, gate.take, table + (e << a.N));
             }
             // (the last block has the caller's stream as well)
             if (i > 0) cube_verify_launch(a, tab, open[(i - 1) & 1], red, d0 + (i - 1) / (rows / step), F32, fan, i < steps ? 1 : 0);
+            if (rest && i == steps && d0 + group >= a.D) rest(fan);
         }
     }
 }
 
 }  // namespace
 
-void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, void* mem,
-                 const std::function<void(hipStream_t)>& beside, hipStream_t s)
+void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, const CubeGate& gate, void* mem,
+                 const std::function<void(hipStream_t)>& beside, const std::function<void(const FanScope&)>& rest, hipStream_t s)
 {
-    if (f32) launch<true>(a, red, kmin, kmax, serial, mem, beside, s);
-    else launch<false>(a, red, kmin, kmax, serial, mem, beside, s);
+    if (f32) launch<true>(a, red, kmin, kmax, serial, gate, mem, beside, rest, s);
+    else launch<false>(a, red, kmin, kmax, serial, gate, mem, beside, rest, s);
 }
 
 }  // namespace thoi

@@ -30,6 +30,9 @@ __global__ __launch_bounds__(kTile) void k_eval_lane(EvalArgs a, PieceTable tab,
     const int N = a.N;
     const int d = blockIdx.y;
     const int64_t blk = blockIdx.x;
+    if constexpr (RED) {
+        if (a.left_out && a.left_out[d]) return;      // uniform
+    }
     const int64_t per_blk = (int64_t)kTile * S * a.seg_tiles;
     // which order / piece does this workgroup belong to (uniform in the workgroup)
     int k = -1;
@@ -242,7 +245,7 @@ bool use_prefix(int engine, bool reduce, bool f64, int N, int k, int64_t D)
 }
 
 template <typename F>
-Plan make_plan(int N, int64_t D, const thoi_nplets* sel, bool reduce, const thoi_eval_opts* o)
+Plan make_plan(int N, int64_t D, const thoi_nplets* sel, bool reduce, const thoi_eval_opts* o, bool few = false)
 {
     const int precision = o->precision, seg_tiles_hint = o->seg_tiles, engine = o->engine;
     Plan P{};
@@ -312,7 +315,8 @@ Plan make_plan(int N, int64_t D, const thoi_nplets* sel, bool reduce, const thoi
     {
         int64_t groups = (reduce ? 8192 : 16384) / (D > 0 ? D : 1);
         groups = groups < 64 ? 64 : groups;
-        const int64_t unit = reduce ? kPairThreads : kPairHalves;
+        // (few: a launch of its own, where the rounds of a workgroup are all there is to wait for)
+        const int64_t unit = !reduce ? kPairHalves : few ? 4 * kPairHalves : kPairThreads;
         int64_t t = (pair_cnt + groups - 1) / groups;
         t = (t + unit - 1) / unit * unit;
         t = t < unit ? unit : t;
@@ -391,9 +395,19 @@ Plan make_plan(int N, int64_t D, const thoi_nplets* sel, bool reduce, const thoi
 
 struct EvalWs {
     size_t refine_off, korder_off, cnt_off, base_off, blk0_off, cursor_off, perm_off;
-    size_t seg_key_off, seg_g_off, seg_hdr_off, late_off, bound_off, clear_end, table_off, total;
+    size_t seg_key_off, seg_g_off, seg_hdr_off, late_off, bound_off, gate_off, clear_end, table_off, total;
     uint32_t refine_cap, seg_cap, late_cap;
 };
+
+// The orders of a RANGE selection up to kc, and those above (g_count 0 when there are none).
+void split_orders(int32_t N, const thoi_nplets* sel, int kc, thoi_nplets& lo, thoi_nplets& hi)
+{
+    lo = hi = *sel;
+    lo.g_count = 0;
+    for (int k = sel->kmin; k <= sel->kmax && k <= kc; ++k) lo.g_count += (int64_t)binom_u64(N, k);
+    hi.g_begin += lo.g_count;
+    hi.g_count -= lo.g_count;
+}
 
 // cube: the layout with the subset table of the cube engine (for calls that want it).
 EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts, bool cube)
@@ -406,6 +420,10 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
         // admission bounds [D][kmax+1][2], cleared with the header
         w.bound_off = off;
         off = align_up(off + (size_t)D * (sel_kmax(sel, N) + 1) * 2 * 8, 256);
+    }
+    if (cube && opts->precision != THOI_FP64) {
+        w.gate_off = off;
+        off = align_up(off + (size_t)D * kCubeGateBytes, 256);
     }
     w.clear_end = off;
     if (opts->precision == THOI_FP32_REFINE) {
@@ -425,13 +443,20 @@ EvalWs eval_layout(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval
     }
     if (reduce && opts->reduce->topk > 0) {
         const int K = opts->reduce->topk;
-        const Plan P = opts->precision == THOI_FP64 ? make_plan<double>(N, D, sel, true, opts)
-                                                    : make_plan<float>(N, D, sel, true, opts);
-        int64_t segs = P.seg_cap * D;
+        int64_t segs;
         if (cube) {
+            // a dataset is the table's or the plan's; orders above the table's (FP32) are the pair engine's
             const bool f32 = opts->precision != THOI_FP64;
-            // orders above the cube engine's stay with the pair engine's plan
-            segs = (cube_segments(N, sel->kmin, cube_kmax(f32, sel->kmax), f32) + (f32 ? P.wblk : 0)) * D;
+            const int kc = cube_kmax(f32, sel->kmax);
+            thoi_nplets lo, hi;
+            split_orders(N, sel, kc, lo, hi);
+            const int64_t table = cube_segments(N, sel->kmin, kc, f32);
+            const int64_t plan = f32 ? make_plan<float>(N, D, &lo, true, opts).seg_cap : 0;
+            segs = ((table > plan ? table : plan) + (hi.g_count ? make_plan<float>(N, D, &hi, true, opts, true).seg_cap : 0)) * D;
+        } else {
+            const Plan P = opts->precision == THOI_FP64 ? make_plan<double>(N, D, sel, true, opts)
+                                                        : make_plan<float>(N, D, sel, true, opts);
+            segs = P.seg_cap * D;
         }
         w.seg_cap = (uint32_t)(segs > 0 ? segs : 1);
         w.seg_key_off = off; off = align_up(off + (size_t)w.seg_cap * 2 * K * 8, 256);
@@ -500,17 +525,12 @@ WaveKernel wave_kernel(bool reduce)
 
 
 template <typename F, int MODE>
-void launch_engines(EvalArgs& a, const Plan& P, const RedArgs& red, hipStream_t s)
+void launch_engines(EvalArgs& a, const Plan& P, const RedArgs& red, const FanScope& fan)
 {
     int ncls = 0;
     const KClass* cls = classes_for<F>(ncls);
     const bool reduce = red.active != 0;
     const int N = a.N;
-    // the class launches are independent: fan them out over side streams
-    int nl = (P.wblk ? 1 : 0) + (P.wblk_hi ? 1 : 0);
-    for (int c = 0; c < ncls; ++c) nl += P.nblk[c] != 0;
-    for (int c = 0; c < P.npcls; ++c) nl += P.pnblk[c] != 0;
-    FanScope fan(s, P.serial ? 1 : nl);
     int b = 0;
     if constexpr (MODE == THOI_SEL_RANGE) {
         for (int c = P.npcls - 1; c >= 0; --c) {      // the longest lanes first
@@ -541,6 +561,17 @@ void launch_engines(EvalArgs& a, const Plan& P, const RedArgs& red, hipStream_t 
         hipLaunchKernelGGL(wk, dim3((unsigned)P.wblk_hi, (unsigned)a.D), dim3(64), lds, fan.stream(b++), a, P.wtab,
                            red, kW2Max + 1, P.wkmax);
     }
+}
+
+template <typename F, int MODE>
+void launch_engines(EvalArgs& a, const Plan& P, const RedArgs& red, hipStream_t s)
+{
+    // the class launches are independent: fan them out over side streams
+    int nl = (P.wblk ? 1 : 0) + (P.wblk_hi ? 1 : 0);
+    for (int c = 0; c < P.ncls; ++c) nl += P.nblk[c] != 0;
+    for (int c = 0; c < P.npcls; ++c) nl += P.pnblk[c] != 0;
+    FanScope fan(s, P.serial ? 1 : nl);
+    launch_engines<F, MODE>(a, P, red, fan);
 }
 
 template <typename F, int MODE>
@@ -623,8 +654,12 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
 {
     EvalWs w = eval_layout(D, N, sel, opts, false);
     if (ws == nullptr || ws_bytes < w.total) return THOI_EWORKSPACE;
-    const bool cube = cube_wanted(N, D, sel, opts) && ws_bytes >= eval_ws_bytes_full(D, N, sel, opts);
-    if (cube) w = eval_layout(D, N, sel, opts, true);
+    bool cube = cube_wanted(N, D, sel, opts);
+    if (cube) {
+        const EvalWs full = eval_layout(D, N, sel, opts, true);
+        cube = ws_bytes >= full.total;
+        if (cube) w = full;
+    }
     char* base = static_cast<char*>(ws);
     const bool reduce = opts->reduce != nullptr;
     EvalArgs a{};
@@ -681,26 +716,40 @@ thoi_status launch_eval(const double* Sigma, int64_t D, int32_t N, const thoi_np
     if (cube) {
         const bool f32 = opts->precision != THOI_FP64;
         const int kc = cube_kmax(f32, sel->kmax);
+        thoi_nplets lo, hi;
+        split_orders(N, sel, kc, lo, hi);
+        CubeGate gate{};
+        const auto args_of = [&](const thoi_nplets& part, const Plan& P) {
+            EvalArgs b = a;
+            b.g_begin = part.g_begin;
+            if (b.flags) b.flags += part.g_begin;
+            b.seg_tiles = P.seg_tiles;
+            b.wave_tile = P.wave_tile;
+            b.wave_tile_hi = P.wave_tile_hi;
+            return b;
+        };
         // the orders above, if any, are few n-plets of the pair engine's, beside the table's build
         std::function<void(hipStream_t)> beside;
-        if (sel->kmax > kc)
+        if (hi.g_count > 0)
             beside = [&](hipStream_t t) {
-                thoi_nplets hi = *sel;
-                for (int k = sel->kmin; k <= kc; ++k) {
-                    hi.g_begin += (int64_t)binom_u64(N, k);
-                    hi.g_count -= (int64_t)binom_u64(N, k);
-                }
-                Plan P = make_plan<float>(N, D, &hi, reduce, opts);
+                Plan P = make_plan<float>(N, D, &hi, reduce, opts, true);
                 P.serial = true;
-                EvalArgs b = a;
-                b.g_begin = hi.g_begin;
-                if (b.flags) b.flags += hi.g_begin;
-                b.seg_tiles = P.seg_tiles;
-                b.wave_tile = P.wave_tile;
-                b.wave_tile_hi = P.wave_tile_hi;
+                EvalArgs b = args_of(hi, P);
                 launch_engines<float, THOI_SEL_RANGE>(b, P, red, t);
             };
-        cube_launch(a, red, sel->kmin, kc, f32, serial, base + w.table_off, beside, s);
+        std::function<void(const FanScope&)> rest;
+        if (f32) {
+            gate.take = reinterpret_cast<uint32_t*>(base + w.gate_off);
+            gate.done = gate.take + D;
+            gate.share = gate.done + D;
+            rest = [&](const FanScope& fan) {
+                const Plan P = make_plan<float>(N, D, &lo, reduce, opts);
+                EvalArgs b = args_of(lo, P);
+                b.left_out = gate.take;
+                launch_engines<float, THOI_SEL_RANGE>(b, P, red, fan);
+            };
+        }
+        cube_launch(a, red, sel->kmin, kc, f32, serial, gate, base + w.table_off, beside, rest, s);
     } else if (opts->precision == THOI_FP64) {
         Plan P = make_plan<double>(N, D, sel, reduce, opts);
         P.serial = serial;

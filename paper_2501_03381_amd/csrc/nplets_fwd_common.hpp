@@ -56,6 +56,7 @@ struct EvalArgs {
     int32_t wave_tile;       // pair engine (orders up to 32 above the lane classes): n-plets per workgroup
     int32_t wave_tile_hi;    // wave engine (orders above 32): n-plets per workgroup
     BiasParams bias;
+    const uint32_t* left_out; // reductions: by dataset, nonzero where another engine takes it; or null
     // LIST / MASK
     const int32_t* idx;
     int32_t kmax_list;

@@ -146,3 +146,72 @@ def test_exchangeable_variables_tie_by_index(env):
             assert np.array_equal(tg[0, k, l, :m], np.arange(g, g + m)) and len(set(tv[0, k, l, :m])) == 1
         assert h[0, k].max() == n == h[0, k].sum()
         g += n
+
+
+def timed(torch, run, n=5):
+    run()
+    best = float("inf")
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def ar1(torch, N, rho):
+    i = torch.arange(N, dtype=torch.float64, device="cuda")
+    return rho ** (i[:, None] - i[None]).abs()
+
+
+def bits(st, *more):
+    return [torch_nan(st.top_val), st.top_g, st.hist, *more]
+
+
+def torch_nan(x):
+    return x.nan_to_num(nan=77.0)
+
+
+# strong autocorrelation, or bins as narrow as FP32's error: most n-plets stay open beside the table, which
+# then costs its own time (a quarter of the call) and that of the separate evaluation; the margin of a third
+# is for a box's noise
+@pytest.mark.parametrize("rho,bins,width", [(0.99, 4096, 4.0), (0.9, 4096, 1.0), (0.999, 0, 1.0)])
+def test_open_nplets_do_not_make_the_call_slower(env, rho, bins, width):
+    torch, api, B, synth = env
+    N = 26
+    S = ar1(torch, N, rho)
+    t, res = {}, {}
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] cube open share rho={rho} bins={bins} {e}", flush=True)
+        kw = dict(orders=(3, N), topk=100, hist_bins=bins, hist_range=(-width, width), engine=e)
+        res[e] = api.nplets_reduce(S, **kw)
+        t[e] = timed(torch, lambda: api.nplets_reduce(S, check=False, **kw))
+    for x, y in zip(bits(res["factor"])[:3 if bins else 2], bits(res["auto"])):
+        assert torch.equal(x, y)
+    assert t["auto"] < 1.33 * t["factor"], t
+
+
+def test_datasets_choose_for_themselves(env):
+    """FP32, several datasets in one call: an easy one, one for the factorisation and one with VIFs around the
+    refinement threshold; every order, flags and device status."""
+    torch, api, B, synth = env
+    N, D = 26, 4
+    rng = np.random.default_rng(5)
+    X = synth.factor_model(rng, 2000, N, 6)
+    Y = X.copy()
+    Y[:, 20] = Y[:, 3] + 0.03 * rng.standard_normal(2000)
+    S = torch.stack([torch.from_numpy(np.cov(X.T)).cuda(), ar1(torch, N, 0.99), torch.from_numpy(np.cov(Y.T)).cuda(),
+                     torch.from_numpy(np.cov(X[:900].T)).cuda()]).contiguous()
+    n = B.thoi_count(N, 3, N)
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] cube FP32 D={D} {e}", flush=True)
+        f = torch.full((D, n), 9, dtype=torch.uint8, device="cuda")
+        st = api.nplets_reduce(S, orders=(3, N), topk=33, hist_bins=1024, hist_range=(-7.3, 5.1), engine=e, flags=f)
+        res.append(bits(st, f))
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
+    refined = (res[1][-1] == B.THOI_NPLET_REFINED).sum(1).tolist()
+    assert refined[0] == refined[1] == refined[3] == 0 and 0 < refined[2] < n
