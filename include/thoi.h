@@ -361,7 +361,10 @@ size_t thoi_workspace_bytes(int32_t which, int64_t D, int64_t T, int32_t N,
  * up to 256 MB) and, behind it, two lists of the n-plets that it leaves open (1.4 GB each at N = 30),
  * instead of factoring every n-plet.  FP32 samples each dataset first and factors every n-plet where the
  * table would leave too many open.
- * Results are the same bit for bit.
+ * Results are those of a factorisation per n-plet (THOI_ENGINE_FACTOR) bit for bit.  For FP32 this rests on its
+ * rounding: Omega and the VIFs of an n-plet S in FP32 within 4 * 2^-24 * |S| * sum_j VIF_j (relative for the VIFs)
+ * of the exact ones; the largest difference measured is 0.15 of those units.  A value further off could be counted
+ * in the bin beside.
  */
 size_t thoi_eval_workspace_bytes_full(int64_t D, int32_t N, const thoi_nplets* sel, const thoi_eval_opts* opts);
 /* Offset in bytes of the int32 device status word inside a workspace. */

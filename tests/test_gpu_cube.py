@@ -215,3 +215,32 @@ def test_datasets_choose_for_themselves(env):
         assert torch.equal(x, y)
     refined = (res[1][-1] == B.THOI_NPLET_REFINED).sum(1).tolist()
     assert refined[0] == refined[1] == refined[3] == 0 and 0 < refined[2] < n
+
+
+def near_singular(torch, synth, N, noise):
+    """A channel recorded twice up to `noise`: half of its n-plets are singular to working precision."""
+    rng = np.random.default_rng(77)
+    X = synth.factor_model(rng, 3000, N, 5)
+    X[:, N - 1] = X[:, 2] + noise * rng.standard_normal(3000)
+    X[:, 12] = X[:, 5] + noise * rng.standard_normal(3000)
+    return torch.from_numpy(np.cov(X.T)).cuda()
+
+
+# whether a pivot near the rounding of 1 is positive is the factorisation's to say, also where the bins are so wide
+# that Omega's place among them is certain
+@pytest.mark.parametrize("noise", [1e-7, 2e-8, 1e-9])
+@pytest.mark.parametrize("bins,topk", [(4, 0), (16, 20)])
+def test_singular_to_working_precision_fp64(env, noise, bins, topk):
+    torch, api, B, synth = env
+    N = 21
+    S = near_singular(torch, synth, N, noise)
+    n = B.thoi_count(N, 3, N)
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] cube near singular noise={noise} bins={bins} topk={topk} {e}", flush=True)
+        f = torch.full((1, n), 9, dtype=torch.uint8, device="cuda")
+        st = api.nplets_reduce(S, orders=(3, N), precision="fp64", topk=topk, hist_bins=bins, hist_range=(-1e9, 1.6e9),
+                               engine=e, flags=f)
+        res.append([f] + ([st.hist] if bins else []) + ([torch_nan(st.top_val), st.top_g] if topk else []))
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
