@@ -244,3 +244,130 @@ def test_singular_to_working_precision_fp64(env, noise, bins, topk):
         res.append([f] + ([st.hist] if bins else []) + ([torch_nan(st.top_val), st.top_g] if topk else []))
     for x, y in zip(*res):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("tau,noise", [(1e5, 3e-3), (1e6, 1e-3), (1e8, 1e-6), (1e8, 1e-5)])
+def test_thresholds_at_the_precision_of_fp32(env, tau, noise):
+    """A refinement threshold where FP32 cannot resolve the VIF: what the table holds above it the FP32
+    factorisation may hold below, so that n-plet is evaluated, not queued on the table's word."""
+    torch, api, B, synth = env
+    N, kmin, kmax = 26, 3, 12
+    rng = np.random.default_rng(8)
+    X = synth.factor_model(rng, 4000, N, 6)
+    X[:, 20] = X[:, 3] + noise * rng.standard_normal(4000)
+    S = torch.from_numpy(np.cov(X.T)).cuda()
+    n = B.thoi_count(N, kmin, kmax)
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] cube tau={tau} noise={noise} {e}", flush=True)
+        f = torch.full((1, n), 9, dtype=torch.uint8, device="cuda")
+        st = api.nplets_reduce(S, orders=(kmin, kmax), topk=100, hist_bins=64, hist_range=(-30, 30), engine=e, flags=f,
+                               vif_tau=tau)
+        res.append((f, st.top_g, st.hist, torch.nan_to_num(st.top_val, nan=77.0)))
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
+
+
+# more datasets than tables at a time, and every order of the largest system in several blocks of rows
+@pytest.mark.parametrize("prec,N,kmin,kmax,D,K", [("fp64", 25, 3, 25, 2, 100), ("fp32_refine", 29, 3, 14, 2, 40),
+                                                  ("fp64", 29, 4, 15, 2, 256), ("fp64", 30, 3, 30, 1, 100)])
+def test_groups_of_tables_and_blocks_of_rows(env, prec, N, kmin, kmax, D, K):
+    torch, api, B, synth = env
+    S = sigma(torch, synth, N, D, 2)
+    res = []
+    for e in ("factor", "auto"):
+        print(f"[gpu-case] cube groups {prec} N={N} orders {kmin}..{kmax} D={D} {e}", flush=True)
+        res.append(bits(api.nplets_reduce(S, orders=(kmin, kmax), topk=K, hist_bins=100, hist_range=(-6, 6), engine=e,
+                                          precision=prec)))
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("prec,N", [("fp64", 22), ("fp32_refine", 26)])
+def test_table_in_a_graph(env, prec, N):
+    torch, api, B, synth = env
+    S = sigma(torch, synth, N, 1, 3)
+    if prec == "fp32_refine":
+        S = torch.stack([S[0], ar1(torch, N, 0.99)]).contiguous()
+    D = S.shape[0]
+    sel = api.range_selection(N, 3, N)
+    st = api.ReduceState(D, N, 50, 128, (-7.3, 5.1), S.device)
+    o = api.make_opts(prec, torch.float32)
+    o.reduce = ctypes.pointer(st.struct)
+    ws = torch.empty(B.thoi_eval_workspace_bytes_full(D, N, sel, o), dtype=torch.uint8, device="cuda")
+
+    def call():
+        B.thoi_reduce_init(st.struct, D, N, api._stream(S.device))
+        B.thoi_nplets_eval(api._ptr(S), D, N, sel, o, None, None, api._ptr(ws), ws.numel(), api._stream(S.device))
+
+    print(f"[gpu-case] cube graph {prec} N={N}", flush=True)
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for i in range(4):
+        S.copy_(S.flip(1).flip(2).contiguous() if i % 2 else S * (1.0 + 0.5 * i))
+        ref = api.nplets_reduce(S, orders=(3, N), topk=50, hist_bins=128, hist_range=(-7.3, 5.1), precision=prec,
+                                engine="factor")
+        g.replay()
+        torch.cuda.synchronize()
+        assert api.device_status(ws) == B.THOI_OK
+        for x, y in zip(bits(ref), bits(st)):
+            assert torch.equal(x, y)
+
+
+def test_table_on_streams_of_several_threads(env):
+    import threading
+    torch, api, B, synth = env
+    N = 22
+    S = [sigma(torch, synth, N, 1, 10 + i) for i in range(3)]
+    kw = dict(orders=(3, N), topk=50, hist_bins=64, hist_range=(-7.3, 5.1), precision="fp64")
+    ref = [bits(api.nplets_reduce(s, engine="factor", **kw)) for s in S]
+    torch.cuda.synchronize()
+    got, err = [[] for _ in S], []
+    print("[gpu-case] cube threads", flush=True)
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(4):
+                    got[i].append(bits(api.nplets_reduce(S[i], **kw)))
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:                   # reported by the test's own thread
+            err.append(e)
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(len(S))]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not err, err
+    for r, runs in zip(ref, got):
+        assert len(runs) == 4
+        for run in runs:
+            for x, y in zip(r, run):
+                assert torch.equal(x, y)
+
+
+def test_no_memory_for_the_table(env, monkeypatch):
+    """A device without the memory for the table: the call takes its least workspace, same results."""
+    torch, api, B, synth = env
+    N = 21
+    S = sigma(torch, synth, N, 1, 4)
+    kw = dict(orders=(3, N), topk=30, hist_bins=64, hist_range=(-7.3, 5.1), precision="fp64")
+    a = bits(api.nplets_reduce(S, **kw))
+    asked, plain = [], api._workspace
+
+    def small(nbytes, device):
+        asked.append(int(nbytes))
+        if len(asked) == 1:
+            raise torch.OutOfMemoryError("no room")
+        return plain(nbytes, device)
+
+    monkeypatch.setattr(api, "_workspace", small)
+    print("[gpu-case] cube without memory", flush=True)
+    b = bits(api.nplets_reduce(S, **kw))
+    assert len(asked) == 2 and asked[1] < asked[0]
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
