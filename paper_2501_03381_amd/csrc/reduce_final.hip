@@ -1,4 +1,5 @@
-// Final merge of the streaming reduction, one workgroup of kFinThreads per (order, dataset, list):
+// Final merge of the streaming reduction, one workgroup of kFinThreads per (order, dataset, list) (where there
+// are many lists of few segments: k_red_final_many):
 // the accumulated list of earlier calls, every segment of this call and the FP64-refined values
 // become the top-K (bottom-K) list.
 //
@@ -25,9 +26,8 @@ static_assert(kFinBuf >= kFinWaves * kRedMaxK && kFinBuf >= kFinThreads, "one ro
 struct RedFinal {
     RedItem list[2][kRedMaxK];                   // the running list, double-buffered
     RedItem buf[kFinBuf];                        // collected entries
-    uint64_t head[kFinSegs];                     // matching segments: the first key of each ...
-    int64_t head_g[kFinSegs];                    // ... its index ...
-    uint32_t seg[kFinSegs];                      // ... and the segment's slot
+    uint64_t head[kFinSegs];                     // matching segments: one key of each ...
+    uint32_t seg[kFinSegs];                      // ... and its slot
     uint32_t rh[256];                            // radix selection
     uint64_t thr;                                // entries behind (thr, thr_g) are not needed
     int64_t thr_g;
@@ -105,12 +105,17 @@ __device__ __forceinline__ uint64_t red_final_select(RedFinal& S, int n, int K)
     return ((uint64_t)S.prefix << 32) | 0xffffffffull;
 }
 
+// Whether a segment of this head may hold an entry that is needed; the index is read where the keys tie.
+__device__ __forceinline__ bool red_final_enters(uint64_t thr, int64_t thr_g, uint64_t head, const int64_t* __restrict__ g)
+{
+    return head < thr || (head == thr && (thr_g == kGEmpty || *g <= thr_g));
+}
+
 // Whole workgroup: the segments [r, n) whose head can still enter, moved to the front; their number.
-__device__ __forceinline__ int red_final_repack(RedFinal& S, int r, int n)
+__device__ __forceinline__ int red_final_repack(RedFinal& S, const RedArgs& red, int l, int K, int r, int n)
 {
     constexpr int kU = kFinSegs / kFinThreads;
     uint64_t h[kU];
-    int64_t g[kU];
     uint32_t s[kU];
     bool on[kU];
 #pragma unroll
@@ -118,9 +123,8 @@ __device__ __forceinline__ int red_final_repack(RedFinal& S, int r, int n)
         const int j = r + (int)threadIdx.x + u * kFinThreads;
         on[u] = j < n;
         h[u] = on[u] ? S.head[j] : 0;
-        g[u] = on[u] ? S.head_g[j] : 0;
         s[u] = on[u] ? S.seg[j] : 0;
-        on[u] = on[u] && !red_less(S.thr, S.thr_g, h[u], g[u]);
+        on[u] = on[u] && red_final_enters(S.thr, S.thr_g, h[u], red.seg_g + ((int64_t)s[u] * 2 + l) * K);
     }
     if (threadIdx.x == 0) S.nseg = 0;
     __syncthreads();
@@ -129,7 +133,6 @@ __device__ __forceinline__ int red_final_repack(RedFinal& S, int r, int n)
         if (on[u]) {
             const int j = atomicAdd(&S.nseg, 1);
             S.head[j] = h[u];
-            S.head_g[j] = g[u];
             S.seg[j] = s[u];
         }
     __syncthreads();
@@ -178,11 +181,9 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
             const uint32_t s = s0 + tid + u * kFinThreads;
             if (h[u].d == d && h[u].k == k) {
                 const uint64_t key = red.seg_key[((int64_t)s * 2 + l) * K];
-                const int64_t g = red.seg_g[((int64_t)s * 2 + l) * K];
-                if (key != kKeyEmpty && !red_less(thr, thr_g, key, g)) {
+                if (key != kKeyEmpty && red_final_enters(thr, thr_g, key, red.seg_g + ((int64_t)s * 2 + l) * K)) {
                     const int j = atomicAdd(&S.nseg, 1);
                     S.head[j] = key;
-                    S.head_g[j] = g;
                     S.seg[j] = s;
                 }
             }
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
             if (nb + kFinWaves * K > kFinBuf) {
                 red_final_flush(S, K);
                 if (sel) {
-                    n = red_final_repack(S, r, n);
+                    n = red_final_repack(S, red, l, K, r, n);
                     r = 0;
                     if (n == 0) break;           // uniform
                 }
@@ -276,11 +277,173 @@ __global__ __launch_bounds__(kFinThreads) void k_red_final(RedArgs red, WsHeader
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same where there are many lists of few segments each: one workgroup of 256 threads and 21 KB of LDS per
+// (order, dataset) for both lists, so seven share a CU and the headers are read once for both; the
+// segments that still beat the running lists are merged one after the other.
+// ------------------------------------------------------------------------------------------------
+struct RedMany {
+    uint64_t key[2][2][kRedMaxK];
+    int64_t g[2][2][kRedMaxK];
+    uint64_t ck[256];
+    int64_t cg[256];
+    int cur[2];
+    int nc;
+};
+
+// Whole workgroup: merge the sorted run (bk, bg)[0..nb) into list `l`, keeping K.
+__device__ __forceinline__ void red_many_merge(RedMany& S, int l, int K, const uint64_t* bk, const int64_t* bg, int nb)
+{
+    const int c = S.cur[l];
+    const uint64_t* ak = S.key[l][c];
+    const int64_t* ag = S.g[l][c];
+    uint64_t* ok = S.key[l][c ^ 1];
+    int64_t* og = S.g[l][c ^ 1];
+    const int na = K;
+    for (int i = threadIdx.x; i < K; i += blockDim.x) {
+        int lo = i - nb > 0 ? i - nb : 0, hi = i < na ? i : na;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (red_less(ak[mid], ag[mid], bk[i - 1 - mid], bg[i - 1 - mid])) lo = mid + 1; else hi = mid;
+        }
+        const int a = lo, b = i - a;
+        const bool takeA = (b >= nb) || (a < na && red_less(ak[a], ag[a], bk[b], bg[b]));
+        ok[i] = takeA ? ak[a] : bk[b];
+        og[i] = takeA ? ag[a] : bg[b];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) S.cur[l] = c ^ 1;
+    __syncthreads();
+}
+
+// Whole workgroup (blockDim <= 256): offer one (key, g) per thread (valid == false: nothing) to
+// list l; the candidates are compacted, sorted (bitonic) and merged.
+__device__ __forceinline__ void red_many_offer(RedMany& S, int l, int K, bool valid, uint64_t key, int64_t g)
+{
+    const int c = S.cur[l];
+    const bool cand = valid && red_less(key, g, S.key[l][c][K - 1], S.g[l][c][K - 1]);
+    if (!__syncthreads_or(cand)) return;
+    if (threadIdx.x == 0) S.nc = 0;
+    __syncthreads();
+    if (cand) {
+        const int slot = atomicAdd(&S.nc, 1);
+        S.ck[slot] = key;
+        S.cg[slot] = g;
+    }
+    __syncthreads();
+    const int nc = S.nc;
+    int P = 1;
+    while (P < nc) P <<= 1;
+    for (int i = nc + threadIdx.x; i < P; i += blockDim.x) { S.ck[i] = kKeyEmpty; S.cg[i] = kGEmpty; }
+    for (int size = 2; size <= P; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            __syncthreads();
+            for (int i = threadIdx.x; i < (P >> 1); i += blockDim.x) {
+                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                const bool asc = (lo & size) == 0;
+                const uint64_t ka = S.ck[lo], kb = S.ck[hi];
+                const int64_t ga = S.cg[lo], gb = S.cg[hi];
+                if (red_less(kb, gb, ka, ga) == asc) { S.ck[lo] = kb; S.ck[hi] = ka; S.cg[lo] = gb; S.cg[hi] = ga; }
+            }
+        }
+    }
+    __syncthreads();
+    red_many_merge(S, l, K, S.ck, S.cg, nc < K ? nc : K);
+}
+
+__global__ __launch_bounds__(256) void k_red_final_many(RedArgs red, WsHeader* hdr)
+{
+    __shared__ RedMany S;
+    const int k = blockIdx.x, d = blockIdx.y;
+    const int K = red.topk;
+    if (K <= 0) return;
+    double* tv = red.top_val + ((int64_t)d * (red.kmax + 1) + k) * 2 * K;
+    int64_t* tg = red.top_g + ((int64_t)d * (red.kmax + 1) + k) * 2 * K;
+    for (int i = threadIdx.x; i < 2 * K; i += blockDim.x) {
+        const int l = i / K, j = i % K;
+        const bool has = tg[i] >= 0;
+        S.key[l][0][j] = has ? red_list_key(l, tv[i]) : kKeyEmpty;
+        S.g[l][0][j] = has ? tg[i] : kGEmpty;
+    }
+    if (threadIdx.x == 0) { S.cur[0] = S.cur[1] = 0; }
+    __syncthreads();
+    // Segments in batches of one per thread: each thread tests its segment's two list heads
+    // against the current K-th entries, the candidates are compacted, and only those are merged
+    // (tested again against the threshold as it tightens).  After the first batches almost no
+    // segment beats the running lists, so a batch costs one round of parallel loads.
+    __shared__ uint32_t cand[2][256];
+    __shared__ int ncand[2];
+    const uint32_t nseg = min(hdr->seg_next, red.seg_cap);
+    for (uint32_t s0 = 0; s0 < nseg; s0 += blockDim.x) {
+        if (threadIdx.x < 2) ncand[threadIdx.x] = 0;
+        __syncthreads();
+        const uint32_t s = s0 + threadIdx.x;
+        if (s < nseg) {
+            const SegHdr h = red.seg_hdr[s];
+            if (h.d == d && h.k == k) {
+                for (int l = 0; l < 2; ++l) {
+                    const int64_t e = ((int64_t)s * 2 + l) * K;
+                    const int c = S.cur[l];
+                    if (red_less(red.seg_key[e], red.seg_g[e], S.key[l][c][K - 1], S.g[l][c][K - 1]))
+                        cand[l][atomicAdd(&ncand[l], 1)] = s;
+                }
+            }
+        }
+        __syncthreads();
+        for (int l = 0; l < 2; ++l) {
+            const int nc = ncand[l];
+            for (int j = 0; j < nc; ++j) {
+                const int64_t e = ((int64_t)cand[l][j] * 2 + l) * K;
+                const uint64_t* bk = red.seg_key + e;
+                const int64_t* bg = red.seg_g + e;
+                const int c = S.cur[l];
+                if (!red_less(bk[0], bg[0], S.key[l][c][K - 1], S.g[l][c][K - 1])) continue;   // uniform
+                red_many_merge(S, l, K, bk, bg, K);
+            }
+        }
+        __syncthreads();                         // every thread has read ncand before the reset
+    }
+    const uint32_t nlate = min(hdr->late_next, red.late_cap);
+    for (uint32_t b0 = 0; b0 < nlate; b0 += blockDim.x) {
+        const uint32_t i = b0 + threadIdx.x;
+        bool mine = false;
+        double v = 0.0;
+        int64_t g = 0;
+        if (i < nlate) {
+            const LateEntry e = red.late[i];
+            mine = e.d == d && e.k == k;
+            v = e.v;
+            g = e.g;
+        }
+        red_many_offer(S, 0, K, mine, red_list_key(0, v), g);
+        red_many_offer(S, 1, K, mine, red_list_key(1, v), g);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * K; i += blockDim.x) {
+        const int l = i / K, j = i % K;
+        const uint64_t key = S.key[l][S.cur[l]][j];
+        const bool has = key != kKeyEmpty;
+        tv[i] = has ? red_list_val(l, key) : __builtin_nan("");
+        tg[i] = has ? S.g[l][S.cur[l]][j] : -1;
+    }
+}
+
+// The second form where a list has a few segments on average, or there are more lists than the first form's
+// workgroups (two per CU) get through in about four rounds.  Whole calls, FP64, K = 100, second / first form, ms:
+//   orders 3..12 of 12 variables (1.4 segments per list): 1 dataset 0.098 / 0.105, 128 0.164 / 0.212, 2000 3.40 / 5.30
+//   orders 3..16 of 16 (15): 1 dataset 0.176 / 0.131, 32 0.465 / 0.442, 128 2.45 / 2.38, 512 9.40 / 10.2
+//   orders 3..6 of 18 (14): 1 dataset 0.156 / 0.096, 128 0.529 / 0.500, 256 0.914 / 0.940
+constexpr int64_t kFewSegments = 4, kManyLists = 1500;
+
 }  // namespace
 
 void red_final_launch(const RedArgs& red, WsHeader* hdr, int kmax, int64_t D, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_red_final, dim3((unsigned)(kmax + 1), (unsigned)D, 2), dim3(kFinThreads), 0, s, red, hdr);
+    const int64_t lists = (int64_t)(kmax + 1) * D;
+    if (lists > kManyLists || (int64_t)red.seg_cap <= kFewSegments * lists)
+        hipLaunchKernelGGL(k_red_final_many, dim3((unsigned)(kmax + 1), (unsigned)D), dim3(256), 0, s, red, hdr);
+    else
+        hipLaunchKernelGGL(k_red_final, dim3((unsigned)(kmax + 1), (unsigned)D, 2), dim3(kFinThreads), 0, s, red, hdr);
 }
 
 }  // namespace thoi
