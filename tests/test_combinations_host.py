@@ -18,6 +18,13 @@ def test_combinations_on_of_more_than_there_are(N, k):
     assert a.dtype == b.dtype and a.shape == b.shape == (0, k)
 
 
+@pytest.mark.parametrize("N,k", [(10, 3), (42, 3), (43, 3), (4, 6)])      # 11,480 and 12,341 rows: either form
+def test_first_rows_are_the_combinations(N, k):
+    from paper_2501_03381_amd import search
+    a, b = search.combinations(N, k), search.first_rows("cpu", N, k).numpy()
+    assert a.dtype == b.dtype and np.array_equal(a, b)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,k", [(100, 3), (100, 4)])
 def test_combinations_on_the_device(N, k):
