@@ -4,10 +4,11 @@
 // runs up to kAnnealSteps iterations, so a whole run is enqueued without a host round trip.
 //
 // Orders up to 32: two chains per 64-lane wavefront, each half-wave factoring its chain's
-// neighbour with the rows in registers (the pair factorisation, entries from Sigma staged in LDS).  Larger orders (up to 64): one wavefront per chain, the block gathered into LDS.  In
-// both, every lane of a chain forms its neighbour from the chain's mask and draws, takes the decision
-// and updates the chain's state, which stays in registers.  Masks are two 64-bit words (N <= 128).  The random
-// numbers are inputs (one row of draws per iteration), so a run is reproducible bit for bit.
+// neighbour with the rows in registers (the pair factorisation, entries from Sigma staged in LDS).
+// Larger orders (up to 64): one wavefront per chain, the block gathered into LDS.  In both, every lane
+// of a chain forms its neighbour from the chain's mask and draws, takes the decision and updates the
+// chain's state, which stays in registers for the launch.  Masks are two 64-bit words (N <= 128).  The
+// random numbers are inputs (one row of draws per iteration), so a run is reproducible bit for bit.
 #include "thoi_internal.hpp"
 #include "nplets_common.hpp"
 #include "pair_factor_lat.hpp"
@@ -214,6 +215,32 @@ __global__ __launch_bounds__(256) void k_anneal_pair(AnnealArgs g, const Mask* _
     if (i == 0 && live) store_chain(g, c, s);
 }
 
+// Omega of the n-plet (w0, w1) by one wavefront, at most kmax members (the clamp keeps a starting mask outside the
+// range of orders in bounds of the block).  A call, not inlined: inside the loop over iterations the compiler
+// unrolled the factorisation's loops otherwise (500 chains of N = 100, 200 iterations, order 64 41.1 ms, 30.8 so; order
+// 40 17.7 and 14.7; one launch per iteration 32.4 and 16.0).
+__device__ __attribute__((noinline)) double wave_omega(GlobalDouble Sigma, int N, uint64_t w0, uint64_t w1, int kmax, LdsDouble sM,
+                                                       LdsDouble sInv, LdsDouble sIsd, LdsInt cidx)
+{
+    const Mask p{{w0, w1}};
+    const int ks = kmax + 1, lane = threadIdx.x & 63;
+    int k = popc(p);
+    k = __builtin_amdgcn_readfirstlane(k < kmax ? k : kmax);
+    // the block's variables and 1/sqrt of their variances, then the correlation block row by row:
+    // R_ij = (Sigma_ij / sqrt(Sigma_ii)) / sqrt(Sigma_jj), unit diagonal
+    int ci = 0;
+    if (lane < k) {
+        ci = nth_set(p, lane);
+        cidx[lane] = ci;
+        sIsd[lane] = inv_sd(Sigma[(int64_t)ci * N + ci]);
+    }
+    __syncthreads();
+    if (lane < k)
+        gather_row((const double*)(Sigma + (int64_t)ci * N), (const int*)cidx, (const double*)sIsd, lane, (double*)(sM + lane * ks));
+    __syncthreads();
+    return omega_of(wave_factor_core(k, (double*)sM, ks, (double*)sInv));
+}
+
 // grid (kappa), block 64: one wavefront per chain, orders up to 64 (otherwise as above).
 // Dynamic LDS: the factorisation block, kmax rows of stride kmax + 1 (sized for the largest order a
 // chain reaches, so that smaller maxima leave room for more wavefronts per CU); static: sInv [64] |
@@ -222,7 +249,6 @@ __global__ __launch_bounds__(64) void k_anneal(AnnealArgs g, const Mask* __restr
                                                double temp, double alpha)
 {
     extern __shared__ double sM[];
-    const int ks = g.kmax + 1;
     __shared__ double sInv[64], sIsd[64];
     __shared__ int cidx[64];
     const int N = g.N;
@@ -238,24 +264,9 @@ __global__ __launch_bounds__(64) void k_anneal(AnnealArgs g, const Mask* __restr
                              : propose(s.cur, N, g.across != 0, g.kmin, g.kmax, dr.move, dr.a, dr.b);
         const double u = dr.u;
         if (t >= 0 && t + 1 < nt) dr = load_draws(g, c, t0 + t + 1);
-        // every state holds k_min..k_max members; the clamp keeps a starting mask outside that range
-        // in bounds of the block
-        int k = popc(p);
-        k = k < g.kmax ? k : g.kmax;
-        // the block's variables and 1/sqrt of their variances, then the correlation block row by row:
-        // R_ij = (Sigma_ij / sqrt(Sigma_ii)) / sqrt(Sigma_jj), unit diagonal
         __syncthreads();                                  // the last factorisation is done with the LDS
-        int ci = 0;
-        if (lane < k) {
-            ci = nth_set(p, lane);
-            cidx[lane] = ci;
-            const double dj = g.Sigma[(int64_t)ci * N + ci];
-            sIsd[lane] = inv_sd(dj);
-        }
-        __syncthreads();
-        if (lane < k) gather_row(g.Sigma + (int64_t)ci * N, cidx, sIsd, lane, sM + lane * ks);
-        __syncthreads();
-        const double om = omega_of(wave_factor_core(k, sM, ks, sInv));
+        const double om = wave_omega((GlobalDouble)g.Sigma, N, p.w[0], p.w[1], g.kmax, (LdsDouble)sM, (LdsDouble)sInv,
+                                     (LdsDouble)sIsd, (LdsInt)cidx);
         if (t < 0) {
             s = Chain{p, p, om, om, 0};
         } else {
