@@ -5,9 +5,10 @@
 //
 // Design: a column is cut into chunks of kChunk samples.  One workgroup of kChunk threads sorts
 // one chunk of (orderable key, sample index) pairs with a bitonic network held in registers:
-// partners inside a wavefront are exchanged by cross-lane shuffles, larger distances through LDS.  With a single chunk the sorted position is the rank.  Otherwise the
-// sorted chunks go to the workspace and a merge workgroup per chunk adds, for each of its
-// elements, the number of entries before it in every chunk of the column (its own included).
+// partners inside a wavefront are exchanged by cross-lane shuffles, larger distances through LDS.
+// With a single chunk the sorted position is the rank.  Otherwise the sorted chunks go to the
+// workspace and a merge workgroup per chunk adds, for each of its elements, the number of entries
+// before it in every chunk of the column (its own included).
 // Every kernel issues its global loads in batches, all in flight together: at these sizes the
 // cost is round trips to memory, not bandwidth.
 #include "thoi_internal.hpp"
@@ -281,22 +282,36 @@ __global__ __launch_bounds__(kMergeThreads) void k_copula_merge(int64_t T, int64
 // chunk sort and merge need 55 exchanges and 10 (nchunks - 1) search steps.
 //
 // Samples are compared by 32-bit codes: the position in [min, max] of the column in units of
-// 2^-32 of the range, a monotone map, so only equal codes need the values themselves (read again
-// from X).  Columns whose samples hold many equal codes (ties, an outlier that squeezes the rest,
-// infinities) take splitters of the full (key, index) pairs, which are distinct, and the upper and
-// lower key words as codes.
+// 2^-32 of the range, a monotone map, and by the next 32 bits of that position where codes are
+// equal.  What the sorted splitter samples show of a column decides:
+//  - hardly any equal codes (continuous values): as above.
+//  - equal codes that are equal values (ties): a bucket per splitter as before, but the samples
+//    equal to one of r equal splitters are dealt to their buckets by index, which is their order.
+//  - many equal codes of different values (an outlier that squeezes the rest), no codes
+//    (infinities, a constant column): splitters of the full (key, index) pairs, which are
+//    distinct, and the key's two words as code.
+// Where equal codes were taken for equal values, or the next bits were equal too, the sorted keys
+// are checked at the end, and a column that does not ascend is ranked again by full keys.
 //
-// 64 datasets of 10,000 x 20: 367 us against 858 us with the chunk sort and merge (ties to one
-// decimal 770, constant columns 450).  About 150 us of it are the strided column reads and writes
-// (a 128-byte line for 8 bytes each), the rest LDS latency; two workgroups per CU (64 registers,
-// spilled, the lower key words in memory) took 339 us there but up to twice the chunk path's time
-// on tied columns.
+// 64 datasets of 10,000 x 20, us, chunk sort and merge 829-855 for all of them: continuous 363,
+// rounded to one decimal 395 and to three 460 (with full keys for every tied column 731 and 728),
+// binary 346 (578), one outlier 477.  About 150 us of it are the strided column reads and writes (a
+// 128-byte line for 8 bytes each), the rest LDS latency.  160 columns of 10,000: chunk path 124,
+// continuous 77, one decimal 81, three 94 (154), binary 69 (123), outlier 100.  The checks cost
+// continuous columns 1% at 10,000 samples and 4% at 3,000 (1280 columns, 126 / 131).  Squeezed
+// columns of 2,049..5,000 samples, fewer than 300 of them, stay slower than the chunk path
+// (288 of 3,000: 82 against 63, continuous ones 54).
 // ------------------------------------------------------------------------------------------------
 constexpr int kColMax = 12288;
 constexpr int kSplit = 1024;
-constexpr int kColMin = 96;                        // one round of columns takes 65-75 us at T = 10,000, the chunk
-                                                   // path 78 us for 80 columns and 127 us for 160
-constexpr int kColTies = 16;                       // equal neighbours among the sorted samples: full keys
+// Columns from which this path is taken, T up to 2048 and above: fewer take about as long as a
+// round of 256, and the chunk path's time grows with them (T = 2048: 21 us up to 128 columns, then
+// 34; T = 10,000: 77 for 96, 95 for 128, 124 for 160).  Below the line tied or squeezed columns
+// lose more than continuous ones gain.
+constexpr int kColMinShort = 144, kColMin = 128;
+// equal neighbours among the sorted splitter samples above which ties and shared codes are told
+// apart, and above which columns of shared codes get full keys
+constexpr int kColTies = 2, kColShared = 16;
 static_assert(kSplit == kSortThreads && kSplit == kChunk, "one splitter per thread");
 
 // LDS: base u32 [kSplit + 2] | wave scratch 4 x f64 [16] | bucket heads u64 [T / 64 + 2] | then codes u32 [T],
@@ -306,7 +321,7 @@ constexpr size_t kColFixed = ((kSplit + 2) * 4 + 15) / 16 * 16 + 4 * 16 * 8;
 inline size_t col_lds_bytes(int64_t T)
 {
     const size_t body = (size_t)T * 10 > kSplit * 12 ? (size_t)T * 10 : kSplit * 12;
-    return kColFixed + (size_t)(T / 64 + 2) * 8 + (body + 15) / 16 * 16;
+    return kColFixed + (size_t)(T / 64 + 2) * 8 + (body + 15) / 16 * 16 + 16;
 }
 
 // the scores of ranks 1..T, once per call, and the cleared header
@@ -341,11 +356,27 @@ __device__ __forceinline__ void bitonic_sort_u32(uint32_t& k, int tid, uint32_t*
     if constexpr (SIZE < kSplit) bitonic_sort_u32<SIZE * 2>(k, tid, sk);
 }
 
+// The compiler no longer knows what n holds (no instruction; the host pass has no scalar registers).
+__device__ __forceinline__ void forget(int64_t& n)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+s"(n));
+#endif
+}
+
+// Number of the sorted splitters s below code c.
+__device__ __forceinline__ int below(const uint32_t* s, uint32_t c)
+{
+    int pos = 0;
+#pragma unroll
+    for (int w = kSplit / 2; w >= 1; w >>= 1) pos += s[pos + w - 1] < c ? w : 0;
+    return pos + (s[pos] < c ? 1 : 0);
+}
+
 // grid (N * D), block kSortThreads; E samples per thread, t = tid + 1024 e.
 template <typename ZT, int E>
-__global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __restrict__ X, int T,
-                                                          int64_t N, void* __restrict__ Z,
-                                                          const double* __restrict__ score, WsHeader* hdr)
+__device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, int64_t N, void* __restrict__ Z,
+                                           const double* __restrict__ score, WsHeader* hdr)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t* base = reinterpret_cast<uint32_t*>(smem);
@@ -355,6 +386,8 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
     uint64_t* spk = reinterpret_cast<uint64_t*>(body);
     uint32_t* spi = reinterpret_cast<uint32_t*>(spk + kSplit);
     uint32_t* spc = reinterpret_cast<uint32_t*>(body);
+    uint64_t* skey = reinterpret_cast<uint64_t*>(spc + kSplit);
+    uint16_t* send = reinterpret_cast<uint16_t*>(skey);
     uint32_t* code = reinterpret_cast<uint32_t*>(body);
     uint32_t* klo = code + T;
     uint16_t* bi = reinterpret_cast<uint16_t*>(klo + T);
@@ -412,28 +445,50 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
     const double scale = 4294967295.0 / (mx - mn);
     auto code_of = [&](double x) { return (uint32_t)((x - mn) * scale); };
     // a constant column, an infinite range or a denormal one has no codes
-    bool full = !(mx > mn) || !(scale > 0.0) || !isfinite(scale);
-    uint32_t sc = 0;
+    bool full = !(mx > mn) || !(scale > 0.0) || !isfinite(scale), tied = false;
     if (!full) {
-        sc = code_of(vs);
+        const uint32_t own = code_of(vs);
+        uint32_t sc = own;
         bitonic_sort_u32<2>(sc, tid, spc);
         __syncthreads();
         spc[tid] = sc;
         __syncthreads();
-        full = __syncthreads_count(tid > 0 && spc[tid - 1] == sc) > kColTies;
+        const bool first = tid == 0 || spc[tid - 1] != sc;
+        const int equal = __syncthreads_count(!first);
+        if (equal > kColTies) {
+            // ties, or different values that share a code?
+            const int a = below(spc, own);
+            skey[a] = order_key(vs);
+            __syncthreads();
+            tied = __syncthreads_or(skey[a] != order_key(vs)) == 0;     // (every lane has read skey)
+            full = !tied && equal > kColShared;
+            if (first) send[tid] = (uint16_t)(sc == 0xffffffffu ? kSplit : below(spc, sc + 1));
+            __syncthreads();
+        }
     }
-    // bucket = number of splitters before the sample (full keys: at or before)
+    uint16_t* srank = reinterpret_cast<uint16_t*>(body);
+    // ranks of the samples v into srank; whether equal codes have to be looked at
+    auto rank_samples = [&](const double (&v)[E], bool full, bool tied) {
+    // bucket = number of splitters before the sample (full keys: at or before) and, of the splitters
+    // equal to it (ties), the share that its index is of T
     int bkt[E];
     uint32_t cd[E];
     if (!full) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             cd[e] = code_of(v[e]);
-            int pos = 0;
+            bkt[e] = below(spc, cd[e]);
+        }
+        if (tied) {
 #pragma unroll
-            for (int s = kSplit / 2; s >= 1; s >>= 1) pos += spc[pos + s - 1] < cd[e] ? s : 0;
-            pos += spc[pos] < cd[e] ? 1 : 0;
-            bkt[e] = pos;
+            for (int e = 0; e < E; ++e) {
+                const int pos = bkt[e] < kSplit ? bkt[e] : kSplit - 1;
+                if (spc[pos] == cd[e]) {
+                    const int r = (int)send[pos] - pos;
+                    const int q = (int)((float)((tid + kSortThreads * e) * (r + 1)) / (float)T);
+                    bkt[e] += q < r ? q : r;
+                }
+            }
         }
     } else {
         uint64_t sk[1] = {order_key(vs)};
@@ -449,7 +504,8 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
             const uint64_t key = order_key(v[e]);
             int pos = 0;
 #pragma unroll
-            for (int s = kSplit / 2; s >= 1; s >>= 1) pos += pair_less(spk[pos + s - 1], spi[pos + s - 1], key, t + 1) ? s : 0;
+            for (int s = kSplit / 2; s >= 1; s >>= 1)
+                pos += pair_less(spk[pos + s - 1], spi[pos + s - 1], key, t + 1) ? s : 0;
             pos += pair_less(spk[pos], spi[pos], key, t + 1) ? 1 : 0;
             bkt[e] = pos;
             cd[e] = (uint32_t)(key >> 32);
@@ -473,7 +529,9 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
         for (int u = 0; u < wv; ++u) before += wsum[u];
         const uint32_t first = before + incl - own;
         base[tid] = first;                         // first position of bucket tid
-        auto mark = [&](uint32_t p) { atomicOr(reinterpret_cast<unsigned long long*>(&heads[p >> 6]), 1ull << (p & 63)); };
+        auto mark = [&](uint32_t p) {
+            atomicOr(reinterpret_cast<unsigned long long*>(&heads[p >> 6]), 1ull << (p & 63));
+        };
         if (own) mark(first);
         if (tid == kSplit - 1) {
             base[kSplit] = before + incl;
@@ -489,7 +547,8 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
             const uint32_t p = base[bkt[e]] + slot[e];
             code[p] = cd[e];
             bi[p] = (uint16_t)t;
-            klo[p] = (uint32_t)order_key(v[e]);
+            const double x = (v[e] - mn) * scale;
+            klo[p] = full ? (uint32_t)order_key(v[e]) : (uint32_t)((x - floor(x)) * 4294967296.0);
         }
     }
     __syncthreads();
@@ -497,6 +556,7 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
     // 64 positions share one word of bucket heads; the bucket that reaches into it and the one that
     // reaches out end in the neighbouring words.
     uint32_t rk[E];                                // rank << 16 | index
+    bool check = tied;                             // equal codes were taken for equal values
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = tid + kSortThreads * e;
@@ -522,40 +582,79 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
             }
             const uint32_t mine = code[p];
             const int t = bi[p];
-            uint32_t less = 0, eq = 0;
-            for (int q = lo; q < hi; ++q) {
-                const uint32_t o = code[q];
-                less += o < mine ? 1u : 0u;
-                eq += o == mine ? 1u : 0u;
-            }
-            if (eq > 1) {
-                // equal codes: by the lower key words (full keys), or by the values themselves
-                if (full) {
+            uint32_t less = 0, eq = 0, alike = 0;
+            if (tied) {                            // uniform: most codes have equals
+                const uint32_t ml = klo[p];
+#pragma unroll 2
+                for (int q = lo; q < hi; ++q) {
+                    const uint32_t o = code[q], ol = klo[q];
+                    const int ot = bi[q];
+                    const bool same = o == mine && ol == ml;
+                    less += (o < mine || (o == mine && ol < ml) || (same && ot < t)) ? 1u : 0u;
+                }
+            } else {
+                for (int q = lo; q < hi; ++q) {
+                    const uint32_t o = code[q];
+                    less += o < mine ? 1u : 0u;
+                    eq += o == mine ? 1u : 0u;
+                }
+                if (eq > 1) {
                     const uint32_t ml = klo[p];
                     for (int q = lo; q < hi; ++q)
                         if (code[q] == mine) {
                             const uint32_t ol = klo[q];
                             less += (ol < ml || (ol == ml && (int)bi[q] < t)) ? 1u : 0u;
-                        }
-                } else {
-                    const uint64_t mk = order_key(Xd[(int64_t)t * N]);
-                    for (int q = lo; q < hi; ++q)
-                        if (code[q] == mine) {
-                            const int ot = bi[q];
-                            less += pair_less(order_key(Xd[(int64_t)ot * N]), (uint32_t)ot, mk, (uint32_t)t) ? 1u : 0u;
+                            alike += ol == ml ? 1u : 0u;
                         }
                 }
             }
+            check = check || alike > 1;
             rk[e] = ((uint32_t)lo + less) << 16 | (uint32_t)t;
         }
     }
-    __syncthreads();
-    // ranks back in sample order, so that consecutive lanes store consecutive rows
-    uint16_t* srank = reinterpret_cast<uint16_t*>(body);
+    check = __syncthreads_or(check && !full) != 0;
+    // back in sample order, so that consecutive lanes store consecutive rows
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (tid + kSortThreads * e < T) srank[rk[e] & 0xffffu] = (uint16_t)(rk[e] >> 16);
     __syncthreads();
+    return check;
+    };
+    if (rank_samples(v, full, tied)) {             // uniform
+        // the keys in the order of the ranks ascend where equal codes were equal values (the samples
+        // are read again: held, they would cost the registers of every column)
+        uint64_t* sorted = reinterpret_cast<uint64_t*>(body + ((size_t)T * 2 + 7) / 8 * 8);
+        double y[E];
+        int64_t n = N;
+        forget(n);                                 // nor are the addresses held
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int t = tid + kSortThreads * e;
+            y[e] = Xd[(int64_t)(t < T ? t : T - 1) * n];
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int t = tid + kSortThreads * e;
+            if (t < T) sorted[srank[t]] = order_key(y[e]);
+        }
+        __syncthreads();
+        bool wrong = false;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int t = tid + kSortThreads * e;
+            if (t < T) {
+                const int r = srank[t];
+                wrong = wrong || (r > 0 && sorted[r - 1] > order_key(y[e]));
+            }
+        }
+        if (__syncthreads_or(wrong)) {             // uniform
+            base[tid] = 0;
+            if (tid < 2) base[kSplit + tid] = 0;
+            for (int i = tid; i < T / 64 + 2; i += kSortThreads) heads[i] = 0;
+            __syncthreads();
+            rank_samples(y, true, false);
+        }
+    }
     double z[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -569,12 +668,28 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
     }
 }
 
+template <typename ZT, int E>
+__global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __restrict__ X, int T, int64_t N,
+                                                             void* __restrict__ Z, const double* __restrict__ score,
+                                                             WsHeader* hdr)
+{
+    copula_col<ZT, E>(X, T, N, Z, score, hdr);
+}
+// Two samples per thread: 64 vector registers let two workgroups of 16 wavefronts share a CU, and
+// the scalar ones have to let them too (1280 columns of 2048: 73 us).
+template <typename ZT>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) void k_copula_col2(
+    const double* __restrict__ X, int T, int64_t N, void* __restrict__ Z, const double* __restrict__ score, WsHeader* hdr)
+{
+    copula_col<ZT, 2>(X, T, N, Z, score, hdr);
+}
+
 template <typename ZT>
 void launch_col(const double* X, int64_t D, int64_t T, int64_t N, void* Z, const double* score, WsHeader* hdr,
                 hipStream_t s)
 {
     typedef void (*ColKernel)(const double*, int, int64_t, void*, const double*, WsHeader*);
-    static const ColKernel kern[] = {k_copula_col<ZT, 2>, k_copula_col<ZT, 4>, k_copula_col<ZT, 6>,
+    static const ColKernel kern[] = {k_copula_col2<ZT>, k_copula_col<ZT, 4>, k_copula_col<ZT, 6>,
                                      k_copula_col<ZT, 8>, k_copula_col<ZT, 10>, k_copula_col<ZT, 12>};
     const int e = (int)((T + kSortThreads - 1) / kSortThreads);
     hipLaunchKernelGGL(kern[(e + 1) / 2 - 1], dim3((unsigned)(N * D)), dim3(kSortThreads), col_lds_bytes(T), s, X, (int)T,
@@ -621,7 +736,7 @@ thoi_status launch_copulize(const double* X, int64_t D, int64_t T, int64_t N, in
     uint32_t* widx = nchunks > 1 ? reinterpret_cast<uint32_t*>(base + w.idx_off) : nullptr;
     int32_t* nanf = nchunks > 1 ? reinterpret_cast<int32_t*>(base + w.nan_off) : nullptr;
 
-    if (nchunks > 1 && T <= kColMax && D * N >= kColMin) {
+    if (nchunks > 1 && T <= kColMax && D * N >= (T <= 2 * kChunk ? kColMinShort : kColMin)) {
         // the score table takes the place of the sorted keys (12 bytes per slot of every column)
         double* score = reinterpret_cast<double*>(base + w.key_off);
         hipLaunchKernelGGL(k_copula_scores, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, T, score, hdr);
