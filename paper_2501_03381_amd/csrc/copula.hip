@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_copula_merge(int64_t T, int64
 // chunk sort and merge need 55 exchanges and 10 (nchunks - 1) search steps.
 //
 // Samples are compared by 32-bit codes: the position in [min, max] of the column in units of
-// 2^-32 of the range, a monotone map, and by the next 32 bits of that position where codes are
+// 2^-32 of the range, a monotone map, and by the next 20 bits of that position where codes are
 // equal.  What the sorted splitter samples show of a column decides:
 //  - hardly any equal codes (continuous values): as above.
 //  - equal codes that are equal values (ties): a bucket per splitter as before, but the samples
@@ -293,14 +293,14 @@ __global__ __launch_bounds__(kMergeThreads) void k_copula_merge(int64_t T, int64
 // Where equal codes were taken for equal values, or the next bits were equal too, the sorted keys
 // are checked at the end, and a column that does not ascend is ranked again by full keys.
 //
-// 64 datasets of 10,000 x 20, us, chunk sort and merge 829-855 for all of them: continuous 363,
-// rounded to one decimal 395 and to three 460 (with full keys for every tied column 731 and 728),
-// binary 346 (578), one outlier 477.  About 150 us of it are the strided column reads and writes (a
+// 64 datasets of 10,000 x 20, us, chunk sort and merge 827-852 for all of them: continuous 367,
+// rounded to one decimal 394 and to three 460 (with full keys for every tied column 730 and 727),
+// binary 341 (576), one outlier 478.  About 150 us of it are the strided column reads and writes (a
 // 128-byte line for 8 bytes each), the rest LDS latency.  160 columns of 10,000: chunk path 124,
-// continuous 77, one decimal 81, three 94 (154), binary 69 (123), outlier 100.  The checks cost
-// continuous columns 1% at 10,000 samples and 4% at 3,000 (1280 columns, 126 / 131).  Squeezed
-// columns of 2,049..5,000 samples, fewer than 300 of them, stay slower than the chunk path
-// (288 of 3,000: 82 against 63, continuous ones 54).
+// continuous 77, one decimal 80, three 94 (155), binary 68 (123), outlier 101.  The checks cost
+// continuous columns 2 to 3%.  Two workgroups share a CU up to 4096 samples: 1280 columns of 3000
+// take 90 against 125 one by one (and 210 by the chunk path).  Squeezed columns, fewer than 300 of
+// them, stay slower than the chunk path from 2,049 to 5,000 samples (160 of 3,000: 45 against 36).
 // ------------------------------------------------------------------------------------------------
 constexpr int kColMax = 12288;
 constexpr int kSplit = 1024;
@@ -443,7 +443,11 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
         mx = wred[16 + u] > mx ? wred[16 + u] : mx;
     }
     const double scale = 4294967295.0 / (mx - mn);
-    auto code_of = [&](double x) { return (uint32_t)((x - mn) * scale); };
+    // the position plus 2^32, a number in [2^32, 2^33): its mantissa is 32 bits before the point (the code)
+    // and 20 after it
+    auto place = [&](double x) { return (uint64_t)__double_as_longlong(fma(x - mn, scale, 4294967296.0)); };
+    auto code_of = [&](double x) { return (uint32_t)(place(x) >> 20); };
+    auto next_bits = [&](double x) { return (uint32_t)place(x); };
     // a constant column, an infinite range or a denormal one has no codes
     bool full = !(mx > mn) || !(scale > 0.0) || !isfinite(scale), tied = false;
     if (!full) {
@@ -472,13 +476,18 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
     // bucket = number of splitters before the sample (full keys: at or before) and, of the splitters
     // equal to it (ties), the share that its index is of T
     int bkt[E];
-    uint32_t cd[E];
+    // code and the next 20 bits, or the key's two words: made together, they let the samples' registers
+    // go (with ten samples and more that spills)
+    constexpr bool kWords = E <= 8;
+    uint32_t cd[E], cl[kWords ? E : 1];
     if (!full) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             cd[e] = code_of(v[e]);
-            bkt[e] = below(spc, cd[e]);
+            if constexpr (kWords) cl[e] = next_bits(v[e]);
         }
+#pragma unroll
+        for (int e = 0; e < E; ++e) bkt[e] = below(spc, cd[e]);
         if (tied) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -509,13 +518,13 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
             pos += pair_less(spk[pos], spi[pos], key, t + 1) ? 1 : 0;
             bkt[e] = pos;
             cd[e] = (uint32_t)(key >> 32);
+            if constexpr (kWords) cl[e] = (uint32_t)key;
         }
     }
     // counting sort by bucket
-    uint32_t slot[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (tid + kSortThreads * e < T) slot[e] = atomicAdd(&base[bkt[e]], 1u);
+    for (int e = 0; e < E; ++e)                    // place in the bucket << 11 | bucket (at most kSplit)
+        if (tid + kSortThreads * e < T) bkt[e] |= (int)(atomicAdd(&base[bkt[e]], 1u) << 11);
     __syncthreads();
     {
         uint32_t* wsum = reinterpret_cast<uint32_t*>(wred);
@@ -544,11 +553,11 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
     for (int e = 0; e < E; ++e) {
         const int t = tid + kSortThreads * e;
         if (t < T) {
-            const uint32_t p = base[bkt[e]] + slot[e];
+            const uint32_t p = base[bkt[e] & 2047] + ((uint32_t)bkt[e] >> 11);
             code[p] = cd[e];
             bi[p] = (uint16_t)t;
-            const double x = (v[e] - mn) * scale;
-            klo[p] = full ? (uint32_t)order_key(v[e]) : (uint32_t)((x - floor(x)) * 4294967296.0);
+            if constexpr (kWords) klo[p] = cl[e];
+            else klo[p] = full ? (uint32_t)order_key(v[e]) : next_bits(v[e]);
         }
     }
     __syncthreads();
@@ -675,13 +684,14 @@ __global__ __launch_bounds__(kSortThreads) void k_copula_col(const double* __res
 {
     copula_col<ZT, E>(X, T, N, Z, score, hdr);
 }
-// Two samples per thread: 64 vector registers let two workgroups of 16 wavefronts share a CU, and
-// the scalar ones have to let them too (1280 columns of 2048: 73 us).
-template <typename ZT>
-__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_num_sgpr(80))) void k_copula_col2(
-    const double* __restrict__ X, int T, int64_t N, void* __restrict__ Z, const double* __restrict__ score, WsHeader* hdr)
+// Up to four samples per thread: 64 vector registers let two workgroups of 16 wavefronts share a
+// CU, and the scalar ones have to let them too.
+template <typename ZT, int E>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8), amdgpu_num_sgpr(80))) void
+k_copula_col2(const double* __restrict__ X, int T, int64_t N, void* __restrict__ Z, const double* __restrict__ score,
+              WsHeader* hdr)
 {
-    copula_col<ZT, 2>(X, T, N, Z, score, hdr);
+    copula_col<ZT, E>(X, T, N, Z, score, hdr);
 }
 
 template <typename ZT>
@@ -689,7 +699,7 @@ void launch_col(const double* X, int64_t D, int64_t T, int64_t N, void* Z, const
                 hipStream_t s)
 {
     typedef void (*ColKernel)(const double*, int, int64_t, void*, const double*, WsHeader*);
-    static const ColKernel kern[] = {k_copula_col2<ZT>, k_copula_col<ZT, 4>, k_copula_col<ZT, 6>,
+    static const ColKernel kern[] = {k_copula_col2<ZT, 2>, k_copula_col2<ZT, 4>, k_copula_col<ZT, 6>,
                                      k_copula_col<ZT, 8>, k_copula_col<ZT, 10>, k_copula_col<ZT, 12>};
     const int e = (int)((T + kSortThreads - 1) / kSortThreads);
     hipLaunchKernelGGL(kern[(e + 1) / 2 - 1], dim3((unsigned)(N * D)), dim3(kSortThreads), col_lds_bytes(T), s, X, (int)T,
