@@ -4,11 +4,13 @@
 // Samples are cut into slabs of kSlab rows.  A workgroup owns one slab and one 16x16 output tile
 // (a0, b0) with b0 >= a0: it stages the slab's 32 columns in LDS (all loads in flight at once),
 // takes their slab means, then contracts the slab-centred columns on the matrix cores
-// (v_mfma_f64_16x16x4_f64), its four waves splitting the slab and summing their tiles through LDS.  The finish kernel combines the slabs with the exact
-// pairwise update of centred sums (Chan, Golub and LeVeque):
+// (v_mfma_f64_16x16x4_f64), its four waves splitting the slab and summing their tiles through LDS.
+// The finish kernel combines the slabs with the exact pairwise update of centred sums (Chan, Golub
+// and LeVeque):
 //   C = sum_s C_s + sum_s n_s (m_s - m)(m_s - m)^T,   m = sum_s n_s m_s / T,
 // with one wavefront per output entry, lanes over slabs and a fixed reduction tree (bitwise
-// reproducible); it divides by T-1 and writes both mirror entries, so Sigma is exactly symmetric.  Both passes are centred, so there is no cancellation of large means.
+// reproducible); it divides by T-1 and writes both mirror entries, so Sigma is exactly symmetric.
+// Both passes are centred, so there is no cancellation of large means.
 #include "thoi_internal.hpp"
 
 namespace thoi {

@@ -219,7 +219,8 @@ __global__ __launch_bounds__(256) void k_anneal_pair(AnnealArgs g, const Mask* _
 // range of orders in bounds of the block).  A call, not inlined: inside the loop over iterations the compiler
 // unrolled the factorisation's loops otherwise (500 chains of N = 100, 200 iterations, order 64 41.1 ms, 30.8 so; order
 // 40 17.7 and 14.7; one launch per iteration 32.4 and 16.0).
-__device__ __attribute__((noinline)) double wave_omega(GlobalDouble Sigma, int N, uint64_t w0, uint64_t w1, int kmax, LdsDouble sM,
+__device__ __attribute__((noinline)) double wave_omega(GlobalDouble Sigma, int N, uint64_t w0, uint64_t w1, int kmax,
+                                                       LdsDouble sM,
                                                        LdsDouble sInv, LdsDouble sIsd, LdsInt cidx)
 {
     const Mask p{{w0, w1}};

@@ -6,9 +6,12 @@
 //   log a_j = log (R_S^-1)_jj = ld(S \ j) - ld(S)
 // (the cofactor identity), and an n-plet costs one pivot and k table reads instead of a factorisation
 // and an inversion of order k ("The combinatorial explosion": the number of subsets stays, the k^3
-// per subset goes).  A reduction needs the value itself of few n-plets, so the table only filters: an n-plet whose bin is certain and which cannot enter a list is counted, the
-// rest is evaluated as the lane and pair engines do (nplets_cube_verify.hip), and the results are theirs
-// bit for bit.
+// per subset goes).  A reduction needs the value itself of few n-plets, so the table only filters: an
+// n-plet whose bin is certain and which cannot enter a list is counted, the rest ("open") is evaluated
+// as the lane and pair engines do (nplets_cube_verify.hip).  The results are theirs bit for bit: in
+// FP64 by an error bound, in FP32 as far as an evaluation errs by no more than its margin assumes
+// (nplets_cube_margin.hpp).  Covariances that would leave most n-plets open are given back to the
+// factorisation by a look at a sample of them (FP32; nplets_cube_gate.hip).
 //
 // A subset is a prefix P (of the first h = N - 10 variables) and one of the 1024 subsets of the last
 // ten; row P of the table holds the latter ordered by size and, within a size, lexicographically.
@@ -22,11 +25,11 @@
 //    removing one of the ten variables stays inside the row (a table of neighbours in LDS).
 // Bound by VALU issue (the build: logarithms and eliminations in FP64; the filter, 57% busy) and the
 // latency of the table reads (k + 1 per n-plet).  A factorisation per n-plet against the table, top-100 and
-// 256 bins, orders 3..N:
-//   N = 30  FP32 + refinement 66.2 / 30.1 ms (build 6.2, filter 22, the rest of the last evaluation)
-//           FP64 424 / 34.2 ms        N = 27  FP32 + refinement 7.74 / 4.12 ms
-//   N = 25  FP64 4.75 / 1.25 ms (build 0.20, bounds 0.09, filter 0.61, open n-plets 0.20, final merge 0.06)
-//   N = 22  FP64 1.66 / 0.51 ms
+// 256 bins, orders 3..N, one dataset, ms:
+//   FP32 + refinement  N = 26  3.80 / 1.97   27  7.34 / 3.60   28  14.6 / 6.80   29  30.3 / 13.4
+//                      N = 30  65.4 / 27.6 (build 6.1, filter 22, open n-plets beside it)
+//   FP64               N = 22  1.11 / 0.43   27  23.4 / 3.88   30  444 / 33.6
+//                      N = 25  4.37 / 1.17 (build 0.20, bounds 0.09, filter 0.61, open n-plets 0.2, merge 0.06)
 // Without bounds of the small orders (their lists open on every n-plet) N = 25 took 1.60 ms, and with an
 // exponential per table read no more and no less.
 // Taking the table's values themselves (no second evaluation) measured 1.05 ms at N = 25, with errors

@@ -61,8 +61,9 @@ int64_t cube_segments(int32_t N, int kmin, int kmax, bool f32);
 // beside (or empty): launches of the call that do not touch the table, put on a stream beside the first
 // table's build.  rest (or empty): a factorisation of every n-plet of kmin..kmax for the datasets that gate.take
 // leaves out.  serial: everything on s.
-void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, const CubeGate& gate, void* mem,
-                 const std::function<void(hipStream_t)>& beside, const std::function<void(const FanScope&)>& rest, hipStream_t s);
+void cube_launch(const EvalArgs& a, const RedArgs& red, int kmin, int kmax, bool f32, bool serial, const CubeGate& gate,
+                 void* mem, const std::function<void(hipStream_t)>& beside,
+                 const std::function<void(const FanScope&)>& rest, hipStream_t s);
 // Decides gate.take from a sample of each dataset's n-plets (FP32).
 void cube_gate_launch(const EvalArgs& a, const CubeTable& tab, const RedArgs& red, const CubeGate& gate, const CubeCost& cost,
                       hipStream_t s);

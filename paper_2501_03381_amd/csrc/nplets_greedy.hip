@@ -23,7 +23,10 @@ namespace thoi {
 namespace {
 
 constexpr int kSelThreads = 1024;
-constexpr int kLatWaves = 2048;         // wavefronts of an order up to which the evaluation is latency-bound
+// Wavefronts of an order up to which the evaluation is latency-bound, two per SIMD.  N = 100, 16
+// solutions, orders 4..32, ms plain / arranged for latency: 800 wavefronts 2.58 / 2.45, 1600 2.65 / 2.64,
+// 2400 2.77 / 2.90, 6400 3.55 / 3.70, 12,800 4.92 / 5.22.
+constexpr int kLatWaves = 2048;
 constexpr int kSelMax = 4096;           // candidates of one order that the selection sorts in LDS
 
 __device__ __forceinline__ bool has(const Mask& m, int v) { return (m.w[v >> 6] >> (v & 63)) & 1ull; }
@@ -125,9 +128,9 @@ __global__ __launch_bounds__(64) void k_greedy_eval(GreedyArgs g, int s, int kc)
 // grid (ceil(kappa * N / 2), D), block 64: two candidate slots per wavefront (half-wave h takes
 // slot 2 blockIdx.x + h), factored with the rows in registers; for steps whose order is at most
 // kW2Max.  The same candidates, measures and sums in variable order as k_greedy_eval.  LAT: the
-// factorisation arranged for latency, for up to about one wavefront per SIMD (N = 100, 16 solutions,
-// one dataset, orders 4..32: 2.03 ms against 2.13); with more of them its registers cost more than it
-// gains (200 datasets of 40 variables, 32 solutions, orders 4..30: 22.3 ms against 20.2).
+// factorisation arranged for latency, for up to kLatWaves wavefronts; with more of them its
+// registers cost more than it gains (also 200 datasets of 40 variables, 32 solutions, orders
+// 4..30: 22.3 ms against 20.2).
 template <bool LAT>
 __global__ __launch_bounds__(64) void k_greedy_eval_pair(GreedyArgs g, int s)
 {
@@ -196,8 +199,7 @@ __device__ __forceinline__ bool sel_before(uint64_t kx, int ix, uint64_t ky, int
 //
 // Selection before sorting: a radix selection over the upper key words (four passes of 8 bits) finds a
 // key that kappa slots reach, and only the slots up to it (kappa and the ties of that word) are
-// sorted.  Sorting all 1600 slots of a step took 19.6 us of which the sort is most; see launch_greedy
-// for the figures.
+// sorted.  1600 slots: 12 us; sorting all of them took 19.6 us, most of it the sort.
 //
 // The sort: bitonic in LDS of the P >= n (a power of two) keys and slots.  Thread
 // 1024 j + 64 w + r of a stage with stride <= 64 exchanges entries of the 128-entry chunk
