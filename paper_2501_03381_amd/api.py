@@ -342,6 +342,8 @@ def nplets_reduce(Sigma: torch.Tensor, *, orders=None, g_range=None, nplets=None
 
     hist_range: (lo, hi) for every order, or an array [kmax+1, 2].  Pass `state` from an
     earlier call to accumulate (e.g. consecutive g_range pieces of one enumeration).
+    Whole orders of 21..30 variables (FP32: 26..30) may use a table of all subsets, up to 12 GB of device
+    memory at 30 variables; where that is not free, or with engine="factor", every n-plet is factored.
     """
     _require_device(Sigma, "Sigma")
     S = (Sigma[None] if Sigma.dim() == 2 else Sigma).contiguous()
