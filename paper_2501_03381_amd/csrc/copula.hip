@@ -13,6 +13,8 @@
 // cost is round trips to memory, not bandwidth.
 #include "thoi_internal.hpp"
 
+#include <type_traits>
+
 namespace thoi {
 namespace {
 
@@ -293,14 +295,15 @@ __global__ __launch_bounds__(kMergeThreads) void k_copula_merge(int64_t T, int64
 // Where equal codes were taken for equal values, or the next bits were equal too, the sorted keys
 // are checked at the end, and a column that does not ascend is ranked again by full keys.
 //
-// 64 datasets of 10,000 x 20, us, chunk sort and merge 827-852 for all of them: continuous 367,
-// rounded to one decimal 394 and to three 460 (with full keys for every tied column 730 and 727),
-// binary 341 (576), one outlier 478.  About 150 us of it are the strided column reads and writes (a
-// 128-byte line for 8 bytes each), the rest LDS latency.  160 columns of 10,000: chunk path 124,
-// continuous 77, one decimal 80, three 94 (155), binary 68 (123), outlier 101.  The checks cost
-// continuous columns 2 to 3%.  Two workgroups share a CU up to 4096 samples: 1280 columns of 3000
-// take 90 against 125 one by one (and 210 by the chunk path).  Squeezed columns, fewer than 300 of
-// them, stay slower than the chunk path from 2,049 to 5,000 samples (160 of 3,000: 45 against 36).
+// 64 datasets of 10,000 x 20, us, chunk sort and merge 827-852 for all of them: continuous 338 (367
+// with the bucket read one entry at a time), rounded to one decimal 394 and to three 460 (with full
+// keys for every tied column 730 and 727), binary 339 (576), one outlier 449.  About 150 us of it are
+// the strided column reads and writes (a 128-byte line for 8 bytes each), the rest LDS latency.  160
+// columns of 10,000: chunk path 124, continuous 70, one decimal 80, three 94 (155), binary 68 (123),
+// outlier 95.  Telling ties apart costs continuous columns 2 to 3%.  Two workgroups share a CU up to
+// 4096 samples: 1280 columns of 3000 take 90 against 125 one by one (and 210 by the chunk path).
+// Squeezed columns, fewer than 300 of them, stay slower than the chunk path from 2,049 to 5,000
+// samples (160 of 3,000: 44 against 36).
 // ------------------------------------------------------------------------------------------------
 constexpr int kColMax = 12288;
 constexpr int kSplit = 1024;
@@ -466,8 +469,10 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
             __syncthreads();
             tied = __syncthreads_or(skey[a] != order_key(vs)) == 0;     // (every lane has read skey)
             full = !tied && equal > kColShared;
-            if (first) send[tid] = (uint16_t)(sc == 0xffffffffu ? kSplit : below(spc, sc + 1));
-            __syncthreads();
+            if (tied) {                            // one past the last of the equal splitters
+                if (first) send[tid] = (uint16_t)(sc == 0xffffffffu ? kSplit : below(spc, sc + 1));
+                __syncthreads();
+            }
         }
     }
     uint16_t* srank = reinterpret_cast<uint16_t*>(body);
@@ -566,6 +571,8 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
     // reaches out end in the neighbouring words.
     uint32_t rk[E];                                // rank << 16 | index
     bool check = tied;                             // equal codes were taken for equal values
+    auto rank_buckets = [&](auto ties) {
+    constexpr bool TIED = decltype(ties)::value;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = tid + kSortThreads * e;
@@ -592,7 +599,7 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
             const uint32_t mine = code[p];
             const int t = bi[p];
             uint32_t less = 0, eq = 0, alike = 0;
-            if (tied) {                            // uniform: most codes have equals
+            if constexpr (TIED) {                  // most codes have equals
                 const uint32_t ml = klo[p];
 #pragma unroll 2
                 for (int q = lo; q < hi; ++q) {
@@ -602,6 +609,7 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
                     less += (o < mine || (o == mine && ol < ml) || (same && ot < t)) ? 1u : 0u;
                 }
             } else {
+#pragma unroll 4
                 for (int q = lo; q < hi; ++q) {
                     const uint32_t o = code[q];
                     less += o < mine ? 1u : 0u;
@@ -621,6 +629,9 @@ __device__ __forceinline__ void copula_col(const double* __restrict__ X, int T, 
             rk[e] = ((uint32_t)lo + less) << 16 | (uint32_t)t;
         }
     }
+    };
+    if (tied) rank_buckets(std::true_type{});      // uniform
+    else rank_buckets(std::false_type{});
     check = __syncthreads_or(check && !full) != 0;
     // back in sample order, so that consecutive lanes store consecutive rows
 #pragma unroll
